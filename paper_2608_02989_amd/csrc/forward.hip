@@ -1,32 +1,32 @@
 // Grouped SwiGLU expert FFN over the restricted routing (Sec. 3.1, Eq. 2):
-// only experts that receive a token are streamed, each exactly once.
+// only experts that receive a token are streamed, each once.
 //
-//   dispatch   one workgroup: per-expert token lists in node order (CSR) and
-//              the list of active experts
-//   gate_up    per (active expert, 16-row tile of I): X_e W_g^T and X_e W_u^T on
-//              MFMA (tokens on the 16-wide M side), SwiGLU in registers, the
-//              activation written once
-//   down       blocks of up to kColMaxT tokens: per 16-column tile of H (and
-//              half of I), act_e W_d^T for every dispatched (expert, 16-token
-//              block), scaled by the gates and summed per token in LDS, then
-//              written to out -- no per-slot buffer, no combine pass.
-//              Larger blocks: per (active expert, 16-row tile of H), scaled
-//              rows to the token's slot row, then
+// Column path (smaller blocks, use_col_path):
+//   gate_up    per (active expert, pair of 16-row tiles of I): X_e W_g^T and
+//              X_e W_u^T on MFMA (tokens on the 16-wide M side), SwiGLU in
+//              registers, the activation written once; the per-expert token
+//              lists are derived in the workgroups
+//   down       per 16-column tile of H (and half of I), act_e W_d^T for every
+//              dispatched (expert, 16-token block), scaled by the gates and
+//              summed per token in LDS, then written to out -- no per-slot
+//              buffer, no combine pass
+// Grouped path (larger blocks):
+//   dispatch   per-expert token lists in node order (CSR) and the GEMM items
+//   gate_up, down   grouped.hip; down writes gate-scaled rows per slot
 //   combine    out_t = sum over the k slots of token t, in slot order
 //
 // Weights are read in the packed fragment layout (see
 // acceptmoe_pack_expert_weights): one wave load = one contiguous 1 KiB block.
 #include <type_traits>
 
-#include "common.hpp"
-#include "launch.hpp"
+#include "ffn_common.hpp"
 
 namespace amoe {
 
 namespace {
 
 constexpr int kDispatchThreads = 1024;
-constexpr int kDispatchChunk = kDispatchThreads;  // nodes per bitmask pass (one per thread)
+constexpr int kDispatchChunk = 256;  // nodes whose positions one dispatch workgroup writes
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -75,26 +75,6 @@ __global__ void pack_gate_up_kernel(const uint4* __restrict__ gate, const uint4*
   }
 }
 
-// A node's routing row, loaded once: experts e[j] and a bit per slot that
-// takes part in the dispatch.  A slot is skipped when its index lies outside
-// [0, E) or repeats the expert of an earlier slot of the same node (a repeated
-// expert is used once, at its first slot).
-template <int KMAX>
-__device__ __forceinline__ uint32_t load_route_row(const int32_t* __restrict__ row, int k, int E,
-                                                   int (&e)[KMAX]) {
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) e[j] = j < k ? row[j] : -1;
-  uint32_t valid = 0u;
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    bool ok = (e[j] >= 0) & (e[j] < E);
-#pragma unroll
-    for (int j2 = 0; j2 < j; ++j2) ok = ok & (e[j2] != e[j]);
-    valid |= ok ? (1u << j) : 0u;
-  }
-  return valid;
-}
-
 // Exclusive scan of per-expert counts and compaction of the active experts,
 // in index order (one wave, lane = tid < 64).  Returns the number of active
 // experts; off[E] = total dispatched slots.
@@ -138,90 +118,88 @@ __device__ __forceinline__ void write_down_items(const ForwardParams& p, const i
   if (tid == 0) *p.n_items = base;
 }
 
+// Items (expert, first CSR row, rows) of the grouped GEMMs: each active
+// expert's rows in equal runs of whole M-tiles, at most p.item_rows rows each,
+// and their count (one wave).  Items of more than p.big_rows rows, which take
+// longest, come first, each group in active-expert order.
+__device__ __forceinline__ void write_grouped_items(const ForwardParams& p, const int* cnt, const int* off,
+                                                    const int* active, int na, int tid) {
+  int base = 0;
+  for (int big = 1; big >= 0; --big) {
+    for (int a0 = 0; a0 < na; a0 += kWave) {
+      const int a = a0 + tid;
+      const int e = a < na ? active[a] : 0;
+      const int c = a < na ? cnt[e] : 0;
+      const int tiles = (c + 15) / 16;
+      const int nb = (c + p.item_rows - 1) / p.item_rows;
+      const int per = nb > 0 ? 16 * ((tiles + nb - 1) / nb) : 16;
+      const int nr = (min(per, c) > p.big_rows) == (big != 0) ? (c + per - 1) / per : 0;  // <= nb
+      const int incl = wave_incl_scan_i32(nr);
+      for (int m = 0; m < nr; ++m)
+        p.items[base + incl - nr + m] = make_int4(e, off[e] + per * m, min(per, c - per * m), 0);
+      base += lane_value(incl, kWave - 1);
+    }
+  }
+  if (tid == 0) *p.n_items = base;
+}
+
 // ---------------------------------------------------------------------------
-// dispatch: CSR of (expert -> slot ids in node order), active expert list.
-// One workgroup; each thread owns one node per pass and keeps its row in
-// registers.  Positions inside an expert's list come from per-expert node
-// bitmasks, so the order is deterministic (node order).
+// dispatch of the grouped path: CSR of (expert -> slot ids in node order) and
+// the items of the grouped GEMMs.  One workgroup per kDispatchChunk nodes.
+// Every workgroup counts all routing rows (LDS atomics; at 1920 nodes x 8
+// slots that is 15 per thread) into the block's totals and into the counts of
+// the nodes before its own, so no workgroup waits for another; positions
+// inside an expert's list then come from per-expert bitmasks of its own
+// nodes, so the order is deterministic (node order).  Workgroup 0 writes the
+// items: an expert's rows in equal runs of whole M-tiles, at most
+// p.item_rows each.
 // ---------------------------------------------------------------------------
 template <int KMAX>
 __global__ __launch_bounds__(kDispatchThreads) void dispatch_kernel(ForwardParams p) {
+  constexpr int words = kDispatchChunk / 32;
   __shared__ int s_cnt[kMaxExperts];
+  __shared__ int s_before[kMaxExperts];
   __shared__ int s_off[kMaxExperts + 1];
-  __shared__ int s_run[kMaxExperts];
   __shared__ int s_active[kMaxExperts];
-  __shared__ int s_nact;
-  __shared__ uint32_t s_mask[kMaxExperts * (kDispatchChunk / 32)];
-  __shared__ int s_pre[kMaxExperts * (kDispatchChunk / 32)];  // nodes of e in the chunk's earlier words
+  __shared__ uint32_t s_mask[kMaxExperts * words];
   const int tid = threadIdx.x;
   const int E = p.E, k = p.k, T = p.T;
-  constexpr int words = kDispatchChunk / 32;
-  for (int e = tid; e < E; e += kDispatchThreads) {
-    s_cnt[e] = 0;
-    s_run[e] = 0;
-  }
+  const int c0 = blockIdx.x * kDispatchChunk;  // first node of this workgroup
+  for (int e = tid; e < E; e += kDispatchThreads) s_cnt[e] = s_before[e] = 0;
+  for (int i = tid; i < E * words; i += kDispatchThreads) s_mask[i] = 0u;
   __syncthreads();
   int ev[KMAX];
-  uint32_t valid = 0u;
   for (int t = tid; t < T; t += kDispatchThreads) {
-    valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t) * k, k, E, ev);
+    const uint32_t valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t) * k, k, E, ev);
+    const int tl = t - c0;
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j)
-      if (valid & (1u << j)) atomicAdd(&s_cnt[ev[j]], 1);
+    for (int j = 0; j < KMAX; ++j) {
+      if (valid & (1u << j)) {
+        atomicAdd(&s_cnt[ev[j]], 1);
+        if (tl < 0) atomicAdd(&s_before[ev[j]], 1);
+        else if (tl < kDispatchChunk) atomicOr(&s_mask[ev[j] * words + (tl >> 5)], 1u << (tl & 31));
+      }
+    }
   }
   __syncthreads();
   if (tid < kWave) {
-    const int na = scan_experts(s_cnt, s_off, s_active, p.active, E, tid);
-    if (tid == 0) {
-      s_nact = na;
-      *p.n_active = na;
-    }
+    const int na = scan_experts(s_cnt, s_off, s_active, nullptr, E, tid);
+    if (blockIdx.x == 0) write_grouped_items(p, s_cnt, s_off, s_active, na, tid);
   }
   __syncthreads();
-  if (p.items != nullptr && tid < kWave) write_down_items(p, s_cnt, s_off, s_active, s_nact, tid);
-  for (int e = tid; e < E; e += kDispatchThreads) {
-    p.cnt[e] = s_cnt[e];
-    p.off[e] = s_off[e];
-  }
-  if (tid == 0) p.off[E] = s_off[E];
-  // position of each slot inside its expert list = earlier nodes of that expert
-  for (int t0 = 0; t0 < T; t0 += kDispatchChunk) {
-    const int t = t0 + tid;
-    for (int i = tid; i < E * words; i += kDispatchThreads) s_mask[i] = 0u;
-    if (t < T && T > kDispatchChunk)
-      valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t) * k, k, E, ev);
-    __syncthreads();
-    if (t < T) {
+  const int t = c0 + tid;
+  if (tid < kDispatchChunk && t < T) {
+    const uint32_t valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t) * k, k, E, ev);
 #pragma unroll
-      for (int j = 0; j < KMAX; ++j)
-        if (valid & (1u << j)) atomicOr(&s_mask[ev[j] * words + (tid >> 5)], 1u << (tid & 31));
-    }
-    __syncthreads();
-    // per expert, exclusive prefix of the word popcounts
-    for (int e = tid; e < E; e += kDispatchThreads) {
-      int c = 0;
-      for (int w = 0; w < words; ++w) {
-        s_pre[e * words + w] = c;
-        c += __popc(s_mask[e * words + w]);
+    for (int j = 0; j < KMAX; ++j) {
+      if (valid & (1u << j)) {
+        const uint32_t* m = s_mask + ev[j] * words;
+        int pos = s_off[ev[j]] + s_before[ev[j]] + __popc(m[tid >> 5] & ((1u << (tid & 31)) - 1u));
+#pragma unroll
+        for (int w = 0; w < words; ++w) pos += w < (tid >> 5) ? __popc(m[w]) : 0;
+        p.ent_slot[pos] = t * k + j;
       }
     }
-    __syncthreads();
-    if (t < T) {
-#pragma unroll
-      for (int j = 0; j < KMAX; ++j) {
-        if (valid & (1u << j)) {
-          const int i = ev[j] * words + (tid >> 5);
-          const int before = s_pre[i] + __popc(s_mask[i] & ((1u << (tid & 31)) - 1u));
-          p.ent_slot[s_off[ev[j]] + s_run[ev[j]] + before] = t * k + j;
-        }
-      }
-    }
-    __syncthreads();
-    for (int e = tid; e < E; e += kDispatchThreads) {
-      const int i = e * words + words - 1;
-      s_run[e] += s_pre[i] + __popc(s_mask[i]);
-    }
-    __syncthreads();
   }
 }
 
@@ -325,112 +303,8 @@ __device__ __forceinline__ void publish_dispatch(const ForwardParams& p, const S
   if (tid < kWave) write_down_items(p, sd.cnt, sd.off, sd.active, sd.nact, tid);
 }
 
-// ---------------------------------------------------------------------------
-// element-type traits for the two MFMA paths
-// ---------------------------------------------------------------------------
-struct Bf16Path {
-  static constexpr int kElemBytes = 2;
-  static constexpr int kKF = 32;  // K elements per 64-byte fragment row chunk
-  // one 16x16x32 MFMA per fragment
-  static __device__ __forceinline__ floatx4 mma(const uint4& a, const uint4& b, floatx4 c) {
-    return mfma_bf16_16x16x32(a, b, c);
-  }
-};
-
-struct F32Path {
-  static constexpr int kElemBytes = 4;
-  static constexpr int kKF = 16;
-  // four 16x16x4 MFMAs per fragment; component j of lane (r, g) is K index 4g + j
-  static __device__ __forceinline__ floatx4 mma(const uint4& a, const uint4& b, floatx4 c) {
-    c = mfma_f32_16x16x4(__uint_as_float(a.x), __uint_as_float(b.x), c);
-    c = mfma_f32_16x16x4(__uint_as_float(a.y), __uint_as_float(b.y), c);
-    c = mfma_f32_16x16x4(__uint_as_float(a.z), __uint_as_float(b.z), c);
-    c = mfma_f32_16x16x4(__uint_as_float(a.w), __uint_as_float(b.w), c);
-    return c;
-  }
-};
-
-__device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
-
-// Tunables (compile-time): k-steps per pipeline stage for small / large
-// M-tile counts; per projection, the output tiles each wave computes on shared
-// A fragments (NTW) and the number of waves splitting a tile's K range (KS).
-#ifndef AMOE_KU_SMALL
-#define AMOE_KU_SMALL 1
-#endif
-#ifndef AMOE_KU_LARGE
-#define AMOE_KU_LARGE 1
-#endif
-#ifndef AMOE_GU_NTW
-#define AMOE_GU_NTW 2
-#endif
-#ifndef AMOE_GU_KS
-#define AMOE_GU_KS 4
-#endif
-// per-slot down pass (blocks of more than 256 tokens): four H-tiles per wave
-// share each activation fragment, two waves split I (against two tiles and
-// four waves: 1036 vs 1103 us for the whole forward at T = 512, H = 4096,
-// I = 1536, where the activation reads had outweighed the weight reads)
-#ifndef AMOE_DN_NTW
-#define AMOE_DN_NTW 4
-#endif
-#ifndef AMOE_DN_KS
-#define AMOE_DN_KS 2
-#endif
-
-// Weight streams.  Every weight fragment is read once per step, through a
-// buffer load whose cache policy is chosen per pass: the gate/up stream is
-// non-temporal; the down stream uses the default policy where H >= 4096 (two
-// column tiles per workgroup, or the per-slot pass) and is non-temporal
-// otherwise.  (Measured on the wide layer, H = 4096, I = 1536: the column-tile
-// down pass takes 68.6 us with default-policy loads against 75.6 us
-// non-temporal, the per-slot down pass at 512 tokens 375 against 396 us; the
-// gate/up pass is fastest non-temporal, 601 against 612 us for plain global
-// non-temporal loads and 621 us with the default policy.  At H = 2048 the
-// default policy saves 0.8 us of the down pass but lets its weights evict the
-// next layer's router planes from the Infinity Cache: the 48-layer pass ran
-// 5027 against 4941 us per block.)  A weight run is addressed by a
-// wave-uniform base and its length in bytes: a load past the run returns
-// zero instead of reading other memory.
-constexpr int kPolicyStream = 2;  // "nt": non-temporal
-constexpr int kPolicyPlain = 0;   // default cache policy
-constexpr int kBufferWord3 = 0x00020000;  // raw (untyped) buffer resource, 32-bit data format
-
-// a pointer the whole wave holds, moved to scalar registers
-__device__ __forceinline__ const uint4* uniform_ptr(const uint4* p) {
-  const uint64_t u = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
-  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
-  return reinterpret_cast<const uint4*>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// 16-byte piece `piece` (lane included) of the run [base, base + bytes)
-template <int kPolicy>
-__device__ __forceinline__ uint4 load_weight(const uint4* base, int bytes, int piece) {
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  __amdgpu_buffer_rsrc_t r =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(base), static_cast<short>(0), bytes, kBufferWord3);
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, piece * 16, 0, kPolicy);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-// k-steps per pipeline stage; two stages are kept in flight
-template <int MT>
-struct Stage {
-  static constexpr int kU = MT <= 2 ? AMOE_KU_SMALL : AMOE_KU_LARGE;
-};
-
-// 16-byte LDS pieces per lane for the shared A stages of any pass with up to
-// MTMAX M-tiles (two stages of kU * MT fragments)
-template <int MTMAX>
-constexpr int shared_a_pieces() {
-  int best = 0;
-  for (int mt = 1; mt <= MTMAX; ++mt) {
-    const int ku = mt <= 2 ? AMOE_KU_SMALL : AMOE_KU_LARGE;
-    best = ku * mt > best ? ku * mt : best;
-  }
-  return 2 * best;
-}
+// k-steps per pipeline stage of the gate/up stream; two stages are kept in flight
+constexpr int kGateUpKU = 1;
 
 // acc[nb][mt] += sum over the K chunks c_i = c_first + i * c_step, 0 <= i < n,
 // of x[mt] (A, tokens) times w[nb] (B, weight rows).  w[nb] is the wave-uniform
@@ -442,7 +316,7 @@ constexpr int shared_a_pieces() {
 template <class P, int MT, int NB, int kPolicy>
 __device__ __forceinline__ void stream_tiles(const uint4* const (&w)[NB], int wbytes, const uint4* const (&x)[MT],
                                              int c_first, int c_step, int n, int wstride, floatx4 (&acc)[NB][MT]) {
-  constexpr int kU = Stage<MT>::kU;
+  constexpr int kU = kGateUpKU;
   const int lane = lane_id();
   uint4 wb0[kU][NB], wb1[kU][NB], xb0[kU][MT], xb1[kU][MT];
   auto load0 = [&](int i) {
@@ -523,227 +397,81 @@ __device__ __forceinline__ void stream_tiles(const uint4* const (&w)[NB], int wb
   }
 }
 
-// acc[nb][mt] as in stream_tiles, for a workgroup whose 4 waves all cover the
-// same K range: each A fragment of a stage is loaded from global memory once,
-// by one of the 4 waves, into a double-buffered LDS stage and read from there
-// by all of them.  Weight fragments stay per wave, two stages in flight.  All
-// 4 waves must call this with the same kc range (it contains barriers).
-template <class P, int MT, int NB, int kPolicy>
-__device__ __forceinline__ void stream_tiles_shared(const uint4* const (&w)[NB], int wbytes,
-                                                    const uint4* const (&x)[MT], int KC, int wstride,
-                                                    floatx4 (&acc)[NB][MT], uint4* xs) {
-  constexpr int kU = Stage<MT>::kU;
-  constexpr int kFr = kU * MT;                   // A fragments per stage
-  constexpr int kMine = (kFr + 3) / 4;           // of which this wave loads
-  const int wave = wave_id(), lane = lane_id();
-  // xs layout: [2 stages][kU][MT][64 lanes] 16-byte pieces
-  auto xs_at = [&](int buf, int u, int mt) { return xs + ((buf * kU + u) * MT + mt) * kWave + lane; };
-  uint4 wb0[kU][NB], wb1[kU][NB], ta[kMine];
-  auto loadw0 = [&](int c) {
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) wb0[u][nb] = load_weight<kPolicy>(w[nb], wbytes, (c + u) * wstride + lane);
-  };
-  auto loadw1 = [&](int c) {
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) wb1[u][nb] = load_weight<kPolicy>(w[nb], wbytes, (c + u) * wstride + lane);
-  };
-  // fragment f of a stage (step f / MT, M-tile f % MT) is loaded by wave f % 4;
-  // every index below is a compile-time constant, the wave test is uniform
-  auto loada = [&](int c) {
-#pragma unroll
-    for (int f = 0; f < kFr; ++f)
-      if ((f & 3) == wave) ta[f >> 2] = x[f % MT][(c + f / MT) * 4];
-  };
-  auto storea = [&](int buf) {
-#pragma unroll
-    for (int f = 0; f < kFr; ++f)
-      if ((f & 3) == wave) *xs_at(buf, f / MT, f % MT) = ta[f >> 2];
-  };
-  auto comp = [&](int buf, uint4 (&wb)[kU][NB]) {
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      uint4 xa[MT];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) xa[mt] = *xs_at(buf, u, mt);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[nb][mt] = P::mma(xa[mt], wb[u][nb], acc[nb][mt]);
-    }
-  };
-  const int nst = KC / kU;  // full stages; a ragged tail follows
-  if (nst > 0) {
-    // stage st lives in LDS buffer st & 1 and registers wb0 / wb1; the
-    // steady state is branch-free, the last one or two stages are peeled
-    loadw0(0);
-    loada(0);
-    storea(0);
-    __syncthreads();
-    int st = 0;
-    for (; st + 2 < nst; st += 2) {
-      loadw1((st + 1) * kU);
-      loada((st + 1) * kU);
-      comp(0, wb0);
-      storea(1);
-      __syncthreads();
-      loadw0((st + 2) * kU);
-      loada((st + 2) * kU);
-      comp(1, wb1);
-      storea(0);
-      __syncthreads();
-    }
-    if (st + 1 < nst) {
-      loadw1((st + 1) * kU);
-      loada((st + 1) * kU);
-      comp(0, wb0);
-      storea(1);
-      __syncthreads();
-      comp(1, wb1);
-    } else {
-      comp(0, wb0);
-    }
-    __syncthreads();  // the LDS stages may be reused by the next pass
-  }
-  for (int c = nst * kU; c < KC; ++c) {
-    uint4 wt[NB], xt[MT];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) wt[nb] = load_weight<kPolicy>(w[nb], wbytes, c * wstride + lane);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) xt[mt] = x[mt][c * 4];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[nb][mt] = P::mma(xt[mt], wt[nb], acc[nb][mt]);
-  }
-}
-
 // ---------------------------------------------------------------------------
-// The two grouped projections share one pass structure.  A workgroup (4
-// waves) owns a run of 16-row output tiles of one active expert.  Each wave
-// computes NTW tiles that share its A fragments; the KS waves of a tile group
-// split the K chunks round-robin (wave s takes chunks s, s + KS, ...; the
-// group reads its weight run front to back together, which keeps the DRAM
+// Gate/up pass (blocks of up to kSelfMaxT tokens).  A workgroup (4 waves) owns
+// one pair of 16-row tiles of I of one active expert, gate and up.  Its waves
+// split the K chunks round-robin (wave s takes chunks s, s + 4, ...; the
+// workgroup reads the pair's weight run front to back, which keeps the DRAM
 // accesses of the whole chip in far fewer open rows than per-wave K ranges)
-// and add their partial tiles in LDS in a fixed order (deterministic), so one
-// workgroup covers 4 * NTW / KS tiles.
-//   GateUp: rows of I, K = H, A = gathered hidden rows; each tile has a gate
-//           and an up fragment; SwiGLU -> act (bf16 for the bf16 path, fp32
-//           otherwise), written once per token row.  NTW = 2: the gate and up
-//           fragments of a tile pair are adjacent in the packed layout
-//           ([E][I/32][K chunk][gate 2p, gate 2p+1, up 2p, up 2p+1]), so a
-//           K chunk of the pair is one 4 KiB run.
-//   Down:   rows of H, K = I, A = act rows of the expert; gate-scaled rows go
-//           to the token's slot row of ys.
+// and add their partial tiles in LDS in a fixed order (deterministic).  The
+// gate and up fragments of a pair are adjacent in the packed layout
+// ([E][I/32][K chunk][gate 2p, gate 2p+1, up 2p, up 2p+1]), so a K chunk of
+// the pair is one 4 KiB run.  A = gathered hidden rows; SwiGLU -> act (bf16
+// for the bf16 path, fp32 otherwise), written once per token row.
 // ---------------------------------------------------------------------------
-enum class Proj { GateUp, Down };
-
-template <Proj F, int NTW, int KS>
-struct ProjShape {
-  static constexpr int kNB = NTW * (F == Proj::GateUp ? 2 : 1);  // weight fragments per k-step
-  static constexpr int kTilesPerWG = 4 * NTW / KS;
-};
+constexpr int kGateUpKS = 4;       // waves splitting K
+constexpr int kTilesPerWG = 2;     // one tile pair
+constexpr int kGateUpFrags = 4;    // weight fragments per K chunk
 
 // ent_e: the n_e slot ids of expert e in node order; o_e: its first row in act
-template <class P, Proj F, int MT, int NTW, int KS, int MG>
-__device__ __forceinline__ void ffn_pass(const ForwardParams& p, const int32_t* ent_e, int e, int tile_base, int n_e,
-                                         int o_e, int m0, floatx4 (*red)[kWave][4], uint4* xs) {
-  static_assert(F != Proj::GateUp || NTW == 2, "the packed gate/up layout holds tile pairs");
-  static_assert(KS % MG == 0, "M groups take waves from the K split");
-  constexpr int NB = ProjShape<F, NTW, KS>::kNB;
-  constexpr int KSe = KS / MG;  // waves per K split of one (tile group, M group)
-  constexpr int TG = 4 / KS;    // tile groups per workgroup
+template <class P, int MT>
+__device__ __forceinline__ void gate_up_pass(const ForwardParams& p, const int32_t* ent_e, int e, int tile0, int n_e,
+                                             int o_e, int m0, floatx4 (*red)[kWave][4]) {
+  constexpr int NB = kGateUpFrags, KS = kGateUpKS;
   const int wave = wave_id(), lane = lane_id();
   const int r = lane & 15, g = lane >> 4;
-  const int sub = wave % KSe;
-  const int tile0 = tile_base + ((wave / KSe) % TG) * NTW;  // first of this wave's NTW tiles
-  m0 += (wave / (KSe * TG)) * MT * 16;                      // this wave's M group
-  const int ntiles = (F == Proj::GateUp ? p.I : p.H) / 16;
-  const int K = F == Proj::GateUp ? p.H : p.I;
-  const int KC = K / P::kKF;
-  const int rowq = K * P::kElemBytes / 16;
+  const int ntiles = p.I / 16;
+  const int KC = p.H / P::kKF;
+  const int rowq = p.H * P::kElemBytes / 16;
 
   const uint4* x[MT];
-  if (F == Proj::GateUp) {
-    const uint4* hid = static_cast<const uint4*>(p.hidden);
-    const int tok0 = ent_e[0] / p.k;  // rows past n_e read a valid row; their outputs are dropped
+  const uint4* hid = static_cast<const uint4*>(p.hidden);
+  const int tok0 = ent_e[0] / p.k;  // rows past n_e read a valid row; their outputs are dropped
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int m = m0 + mt * 16 + r;
-      const int tok = m < n_e ? ent_e[m] / p.k : tok0;
-      x[mt] = hid + static_cast<size_t>(tok) * rowq + g;
-    }
-  } else {
-    const uint4* act = static_cast<const uint4*>(p.act);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int m = m0 + mt * 16 + r;
-      x[mt] = act + static_cast<size_t>(o_e + (m < n_e ? m : 0)) * rowq + g;
-    }
+  for (int mt = 0; mt < MT; ++mt) {
+    const int m = m0 + mt * 16 + r;
+    const int tok = m < n_e ? ent_e[m] / p.k : tok0;
+    x[mt] = hid + static_cast<size_t>(tok) * rowq + g;
   }
-  // tiles past the end are clamped to a valid tile (pair): computed, never written
-  const uint4* w[NB];  // wave-uniform starts of the weight runs
-  int wstride;         // 16-byte pieces from one K chunk to the next
-  int wbytes;          // bytes of each run from its start
-  if (F == Proj::GateUp) {
-    const int npairs = (ntiles + 1) / 2;
-    const int pair = min(tile0 / 2, npairs - 1);
-    const uint4* base = uniform_ptr(static_cast<const uint4*>(p.w_gate_up) +
-                                    (static_cast<size_t>(e) * npairs + pair) * KC * 4 * kWave);
-    w[0] = base;              // gate, tile 2 pair
-    w[1] = base + 2 * kWave;  // up, tile 2 pair
-    w[2] = base + kWave;      // gate, tile 2 pair + 1
-    w[3] = base + 3 * kWave;  // up, tile 2 pair + 1
-    wstride = 4 * kWave;
-    wbytes = KC * 4 * kWave * 16 - 3 * kWave * 16;  // the last fragment of w[3] ends the pair's run
-  } else {
-#pragma unroll
-    for (int j = 0; j < NTW; ++j) {
-      const int tile = min(tile0 + j, ntiles - 1);
-      w[j] = uniform_ptr(static_cast<const uint4*>(p.w_down) + (static_cast<size_t>(e) * ntiles + tile) * KC * kWave);
-    }
-    wstride = kWave;
-    wbytes = KC * kWave * 16;
-  }
-  constexpr int kPolicy = F == Proj::GateUp ? kPolicyStream : kPolicyPlain;
+  // wave-uniform starts of the weight runs
+  const int npairs = (ntiles + 1) / 2;
+  const uint4* base = uniform_ptr(static_cast<const uint4*>(p.w_gate_up) +
+                                  (static_cast<size_t>(e) * npairs + tile0 / 2) * KC * 4 * kWave);
+  const uint4* w[NB];
+  w[0] = base;              // gate, tile 2 pair
+  w[1] = base + 2 * kWave;  // up, tile 2 pair
+  w[2] = base + kWave;      // gate, tile 2 pair + 1
+  w[3] = base + 3 * kWave;  // up, tile 2 pair + 1
+  const int wstride = 4 * kWave;                                // 16-byte pieces from one K chunk to the next
+  const int wbytes = KC * 4 * kWave * 16 - 3 * kWave * 16;      // the last fragment of w[3] ends the pair's run
   floatx4 acc[NB][MT];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[nb][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (KS == 1 && MG == 1)
-    stream_tiles_shared<P, MT, NB, kPolicy>(w, wbytes, x, KC, wstride, acc, xs);
-  else
-    stream_tiles<P, MT, NB, kPolicy>(w, wbytes, x, sub, KSe, (KC - sub + KSe - 1) / KSe, wstride, acc);
+  stream_tiles<P, MT, NB, kPolicyStream>(w, wbytes, x, wave, KS, (KC - wave + KS - 1) / KS, wstride, acc);
 
-  if constexpr (KSe > 1) {
-    // fixed-order sum of the KS partial tiles, four fragments per LDS round
+  // fixed-order sum of the KS partial tiles, four fragments per LDS round
 #pragma unroll
-    for (int q0 = 0; q0 < NB * MT; q0 += 4) {
+  for (int q0 = 0; q0 < NB * MT; q0 += 4) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (q0 + q < NB * MT) red[wave][lane][q] = acc[(q0 + q) / MT][(q0 + q) % MT];
-      __syncthreads();
-      if (sub == 0) {
+    for (int q = 0; q < 4; ++q) red[wave][lane][q] = acc[(q0 + q) / MT][(q0 + q) % MT];
+    __syncthreads();
+    if (wave == 0) {
 #pragma unroll
-        for (int s2 = 1; s2 < KSe; ++s2)
+      for (int s2 = 1; s2 < KS; ++s2)
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (q0 + q < NB * MT) {
-              const floatx4 v = red[wave + s2][lane][q];
+        for (int q = 0; q < 4; ++q) {
+          const floatx4 v = red[s2][lane][q];
 #pragma unroll
-              for (int i = 0; i < 4; ++i) acc[(q0 + q) / MT][(q0 + q) % MT][i] += v[i];
-            }
-      }
-      __syncthreads();
+          for (int i = 0; i < 4; ++i) acc[(q0 + q) / MT][(q0 + q) % MT][i] += v[i];
+        }
     }
+    __syncthreads();
   }
-  if (sub == 0) {
+  if (wave == 0) {
 #pragma unroll
-    for (int j = 0; j < NTW; ++j) {
+    for (int j = 0; j < kTilesPerWG; ++j) {
       const int tile = tile0 + j;
       if (tile >= ntiles) continue;
 #pragma unroll
@@ -752,17 +480,12 @@ __device__ __forceinline__ void ffn_pass(const ForwardParams& p, const int32_t* 
         for (int i = 0; i < 4; ++i) {
           const int m = m0 + mt * 16 + 4 * g + i;
           if (m < n_e) {
-            if (F == Proj::GateUp) {
-              const float v = silu_mul(acc[2 * j][mt][i], acc[2 * j + 1][mt][i]);
-              const size_t idx = static_cast<size_t>(o_e + m) * p.I + tile * 16 + r;
-              if (P::kElemBytes == 2)
-                static_cast<uint16_t*>(p.act)[idx] = float_to_bf16_bits(v);
-              else
-                static_cast<float*>(p.act)[idx] = v;
-            } else {
-              const int s = ent_e[m];
-              p.ys[static_cast<size_t>(s) * p.H + tile * 16 + r] = p.topk_gate[s] * acc[j][mt][i];
-            }
+            const float v = silu_mul(acc[2 * j][mt][i], acc[2 * j + 1][mt][i]);
+            const size_t idx = static_cast<size_t>(o_e + m) * p.I + tile * 16 + r;
+            if (P::kElemBytes == 2)
+              static_cast<uint16_t*>(p.act)[idx] = float_to_bf16_bits(v);
+            else
+              static_cast<float*>(p.act)[idx] = v;
           }
         }
       }
@@ -771,21 +494,14 @@ __device__ __forceinline__ void ffn_pass(const ForwardParams& p, const int32_t* 
 }
 
 // the full CSR is built only by the publishing workgroup, after its items
-template <bool kSelf, int KMAX>
-union SelfDispatchSlot {
+template <int KMAX>
+union DispatchSlot {
   SelfDispatch sd;
   ItemDispatch<KMAX> id;
 };
-template <int KMAX>
-union SelfDispatchSlot<false, KMAX> {
-  int unused;
-};
 
 // Work item i = (active expert i / wg_per_expert, tile run i % wg_per_expert).
-// Without kSelf: grid.x = cap_experts * wg_per_expert, one item per
-// workgroup, reading dispatch_kernel's CSR.  kSelf (gate/up pass, blocks of up
-// to kSelfMaxT tokens): a grid of up to kSelfGridMult times the workgroups
-// resident at once (H >= 4096; once otherwise) takes items blockIdx.x,
+// A grid of up to kSelfGridMult times the workgroups resident at once (H >= 4096; once otherwise) takes items blockIdx.x,
 // blockIdx.x + gridDim.x, ..., each with its own per-item dispatch.  The
 // workgroups beyond the resident ones start on whichever CU frees a slot
 // first, which evens out the CUs' finish times (CUs stream at up to 20 %
@@ -802,16 +518,14 @@ constexpr int kSelfGridMult = 3;
 
 // Occupancy floor: three workgroups per CU for up to two M-tiles, two for
 // more (the register budget the streaming loop is tuned to).
-template <class P, Proj F, int MTMAX, int NTW, int KS, bool kSelf, int KMAX>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MTMAX <= 2 ? 3 : 2))) void ffn_kernel(
+template <class P, int MTMAX, int KMAX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MTMAX <= 2 ? 3 : 2))) void gate_up_kernel(
     ForwardParams p) {
-  __shared__ floatx4 red[KS > 1 ? 4 : 1][kWave][4];
-  __shared__ uint4 xs[KS == 1 ? shared_a_pieces<MTMAX>() * kWave : 1];
-  __shared__ SelfDispatchSlot<kSelf, KMAX> sds;
-  constexpr int tpw = ProjShape<F, NTW, KS>::kTilesPerWG;
-  const int ntiles = (F == Proj::GateUp ? p.I : p.H) / 16;
-  const int wg_per_expert = (ntiles + tpw - 1) / tpw;
-  if (F == Proj::GateUp && p.zero_out) {
+  __shared__ floatx4 red[kGateUpKS][kWave][4];
+  __shared__ DispatchSlot<KMAX> ds;
+  const int ntiles = p.I / 16;
+  const int wg_per_expert = (ntiles + kTilesPerWG - 1) / kTilesPerWG;
+  if (p.zero_out) {
     // the column-tile down pass adds its two halves of I into out
     float4* o4 = reinterpret_cast<float4*>(p.out);
     const size_t n4 = static_cast<size_t>(p.T) * p.H / 4;
@@ -819,114 +533,82 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MTMAX <= 2 
          i += static_cast<size_t>(gridDim.x) * blockDim.x)
       o4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  // An expert with more than MTMAX M-tiles of tokens would stream its weights
-  // once per MTMAX M-tiles.  Without the in-workgroup dispatch (blocks of more
-  // than kSelfMaxT tokens) such an expert instead takes the waves of the K
-  // split as M groups: MG = 2 or 4 groups of MT M-tiles each read the same
-  // weight fragments (from L1 or L2 after the first), so the weights come
-  // from HBM once per up to 4 MTMAX M-tiles.  At 512 tokens (8 trees of 64,
-  // H = 4096) experts receive up to ~160 tokens and the forward took 1014.5
-  // us with one pass per MTMAX M-tiles, 972.3 us with M groups.  Every wave
-  // of the workgroup runs the same instantiation (the passes hold barriers).
-  auto pass_mt = [&](auto mg_tag, int mt, int tile_base, int e, int n_e, int o_e, int m0, const int32_t* ent_e) {
-    constexpr int G = decltype(mg_tag)::value;
-    if (mt == 1) ffn_pass<P, F, 1, NTW, KS, G>(p, ent_e, e, tile_base, n_e, o_e, m0, red, xs);
-    else if (MTMAX >= 2 && mt == 2) ffn_pass<P, F, (MTMAX >= 2 ? 2 : 1), NTW, KS, G>(p, ent_e, e, tile_base, n_e, o_e, m0, red, xs);
-    else if (MTMAX >= 3 && mt == 3) ffn_pass<P, F, (MTMAX >= 3 ? 3 : 1), NTW, KS, G>(p, ent_e, e, tile_base, n_e, o_e, m0, red, xs);
-    else ffn_pass<P, F, MTMAX, NTW, KS, G>(p, ent_e, e, tile_base, n_e, o_e, m0, red, xs);
-  };
-  auto run_expert = [&](int tile_base, int e, int n_e, int o_e, const int32_t* ent_e) {
-    for (int m0 = 0; m0 < n_e;) {
-      const int left = (n_e - m0 + 15) / 16;  // M-tiles still to cover
-      if (kSelf || left <= MTMAX || KS % 2 != 0) {
-        const int mt = min(MTMAX, left);
-        pass_mt(std::integral_constant<int, 1>{}, mt, tile_base, e, n_e, o_e, m0, ent_e);
-        m0 += 16 * mt;
-      } else if (KS % 4 == 0 && left > 2 * MTMAX) {
-        const int mt = (min(left, 4 * MTMAX) + 3) / 4;
-        pass_mt(std::integral_constant<int, (KS % 4 == 0 ? 4 : 1)>{}, mt, tile_base, e, n_e, o_e, m0, ent_e);
-        m0 += 64 * mt;
-      } else {
-        const int mt = (min(left, 2 * MTMAX) + 1) / 2;
-        pass_mt(std::integral_constant<int, (KS % 2 == 0 ? 2 : 1)>{}, mt, tile_base, e, n_e, o_e, m0, ent_e);
-        m0 += 32 * mt;
-      }
+  auto run_expert = [&](int tile0, int e, int n_e, int o_e, const int32_t* ent_e) {
+    for (int m0 = 0; m0 < n_e; m0 += 16 * MTMAX) {
+      const int mt = min(MTMAX, (n_e - m0 + 15) / 16);
+      if (mt == 1) gate_up_pass<P, 1>(p, ent_e, e, tile0, n_e, o_e, m0, red);
+      else if (MTMAX >= 2 && mt == 2) gate_up_pass<P, (MTMAX >= 2 ? 2 : 1)>(p, ent_e, e, tile0, n_e, o_e, m0, red);
+      else if (MTMAX >= 3 && mt == 3) gate_up_pass<P, (MTMAX >= 3 ? 3 : 1)>(p, ent_e, e, tile0, n_e, o_e, m0, red);
+      else gate_up_pass<P, MTMAX>(p, ent_e, e, tile0, n_e, o_e, m0, red);
     }
   };
-  if constexpr (kSelf) {
-    ItemDispatch<KMAX>& id = sds.id;
-    const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
-    const int T = p.T, k = p.k, E = p.E, words = (E + 31) / 32;
-    if (tid < kMaxExperts / 32) id.emask[tid] = 0u;
-    {
-      int ev[KMAX];
+  ItemDispatch<KMAX>& id = ds.id;
+  const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
+  const int T = p.T, k = p.k, E = p.E, words = (E + 31) / 32;
+  if (tid < kMaxExperts / 32) id.emask[tid] = 0u;
+  {
+    int ev[KMAX];
 #pragma unroll
-      for (int j = 0; j < KMAX; ++j) ev[j] = -1;
-      uint32_t valid = 0u;
-      if (tid < T) {
-        valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(tid) * k, k, E, ev);
+    for (int j = 0; j < KMAX; ++j) ev[j] = -1;
+    uint32_t valid = 0u;
+    if (tid < T) {
+      valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(tid) * k, k, E, ev);
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j) id.row[tid][j] = ev[j];
-        id.valid[tid] = valid;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < KMAX; ++j)
-        if (valid & (1u << j)) atomicOr(&id.emask[ev[j] >> 5], 1u << (ev[j] & 31));
+      for (int j = 0; j < KMAX; ++j) id.row[tid][j] = ev[j];
+      id.valid[tid] = valid;
     }
     __syncthreads();
-    // workgroup-uniform values go to scalar registers (the streaming loop
-    // needs every vector register it can get)
-    int nact = 0;
-    for (int w = 0; w < words; ++w) nact += __popc(id.emask[w]);
-    nact = __builtin_amdgcn_readfirstlane(nact);
-    const int n_items = nact * wg_per_expert;
-    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-      const int e = __builtin_amdgcn_readfirstlane(nth_set_bit(id.emask, words, item / wg_per_expert));
-      // this thread's token: its slot of e, and its slots of lower experts
-      int slot = -1, less = 0;
-      if (tid < T) {
-        const uint32_t valid = id.valid[tid];
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j) {
-          const int ej = id.row[tid][j];
-          if (valid & (1u << j)) {
-            slot = ej == e ? static_cast<int>(tid) * k + j : slot;
-            less += ej < e ? 1 : 0;
-          }
+    for (int j = 0; j < KMAX; ++j)
+      if (valid & (1u << j)) atomicOr(&id.emask[ev[j] >> 5], 1u << (ev[j] & 31));
+  }
+  __syncthreads();
+  // workgroup-uniform values go to scalar registers (the streaming loop
+  // needs every vector register it can get)
+  int nact = 0;
+  for (int w = 0; w < words; ++w) nact += __popc(id.emask[w]);
+  nact = __builtin_amdgcn_readfirstlane(nact);
+  const int n_items = nact * wg_per_expert;
+  for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+    const int e = __builtin_amdgcn_readfirstlane(nth_set_bit(id.emask, words, item / wg_per_expert));
+    // this thread's token: its slot of e, and its slots of lower experts
+    int slot = -1, less = 0;
+    if (tid < T) {
+      const uint32_t valid = id.valid[tid];
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j) {
+        const int ej = id.row[tid][j];
+        if (valid & (1u << j)) {
+          slot = ej == e ? static_cast<int>(tid) * k + j : slot;
+          less += ej < e ? 1 : 0;
         }
       }
-      const uint64_t hm = __ballot(slot >= 0);
-      const int wless = wave_sum_i32(less);
-      __syncthreads();  // the previous item's list is no longer read
-      if (lane == 0) {
-        id.wcnt[wave] = popc64(hm);
-        id.wless[wave] = wless;
-      }
-      __syncthreads();
-      int before = 0, n_e = 0, o_e = 0;
+    }
+    const uint64_t hm = __ballot(slot >= 0);
+    const int wless = wave_sum_i32(less);
+    __syncthreads();  // the previous item's list is no longer read
+    if (lane == 0) {
+      id.wcnt[wave] = popc64(hm);
+      id.wless[wave] = wless;
+    }
+    __syncthreads();
+    int before = 0, n_e = 0, o_e = 0;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        before += w < wave ? id.wcnt[w] : 0;
-        n_e += id.wcnt[w];
-        o_e += id.wless[w];
-      }
-      if (slot >= 0) id.ent[before + popc64(hm & lanes_below(lane))] = slot;
-      __syncthreads();
-      run_expert((item % wg_per_expert) * tpw, e, __builtin_amdgcn_readfirstlane(n_e),
-                 __builtin_amdgcn_readfirstlane(o_e), id.ent);
+    for (int w = 0; w < 4; ++w) {
+      before += w < wave ? id.wcnt[w] : 0;
+      n_e += id.wcnt[w];
+      o_e += id.wless[w];
     }
-    if (blockIdx.x == 0) {
-      __syncthreads();  // the per-item state shares this LDS
-      SelfDispatch& sd = sds.sd;
-      self_dispatch<KMAX>(p, sd, tid);
-      publish_dispatch(p, sd, tid);
-    }
-  } else {
-    if (static_cast<int>(blockIdx.x) >= *p.n_active * wg_per_expert) return;
-    const int a = blockIdx.x / wg_per_expert;
-    const int e = p.active[a];
-    run_expert((blockIdx.x % wg_per_expert) * tpw, e, p.cnt[e], p.off[e], p.ent_slot + p.off[e]);
+    if (slot >= 0) id.ent[before + popc64(hm & lanes_below(lane))] = slot;
+    __syncthreads();
+    run_expert((item % wg_per_expert) * kTilesPerWG, e, __builtin_amdgcn_readfirstlane(n_e),
+               __builtin_amdgcn_readfirstlane(o_e), id.ent);
+  }
+  if (blockIdx.x == 0) {
+    __syncthreads();  // the per-item state shares this LDS
+    SelfDispatch& sd = ds.sd;
+    self_dispatch<KMAX>(p, sd, tid);
+    publish_dispatch(p, sd, tid);
   }
 }
 
@@ -1159,28 +841,17 @@ int resident_workgroups() {
 }
 
 template <class P, int MTMAX>
-hipError_t launch_gate_up(const ForwardParams& p, int cap, bool self, hipStream_t stream) {
-  constexpr int gt = ProjShape<Proj::GateUp, AMOE_GU_NTW, AMOE_GU_KS>::kTilesPerWG;
-  const int items = cap * ((p.I / 16 + gt - 1) / gt);
-  if (!self) {
-    ffn_kernel<P, Proj::GateUp, MTMAX, AMOE_GU_NTW, AMOE_GU_KS, false, 8><<<dim3(items), 256, 0, stream>>>(p);
-  } else if (p.k <= 8) {
-    constexpr auto kern = &ffn_kernel<P, Proj::GateUp, MTMAX, AMOE_GU_NTW, AMOE_GU_KS, true, 8>;
+hipError_t launch_gate_up(const ForwardParams& p, int cap, hipStream_t stream) {
+  const int items = cap * ((p.I / 16 + kTilesPerWG - 1) / kTilesPerWG);
+  if (p.k <= 8) {
+    constexpr auto kern = &gate_up_kernel<P, MTMAX, 8>;
     const int res = (p.H >= 4096 ? kSelfGridMult : 1) * resident_workgroups<kern>();
     kern<<<dim3(items < res ? items : res), 256, 0, stream>>>(p);
   } else {
-    constexpr auto kern = &ffn_kernel<P, Proj::GateUp, MTMAX, AMOE_GU_NTW, AMOE_GU_KS, true, kMaxTopK>;
+    constexpr auto kern = &gate_up_kernel<P, MTMAX, kMaxTopK>;
     const int res = (p.H >= 4096 ? kSelfGridMult : 1) * resident_workgroups<kern>();
     kern<<<dim3(items < res ? items : res), 256, 0, stream>>>(p);
   }
-  return hipGetLastError();
-}
-
-template <class P, int MTMAX>
-hipError_t launch_down_rows(const ForwardParams& p, int cap, hipStream_t stream) {
-  constexpr int dt = ProjShape<Proj::Down, AMOE_DN_NTW, AMOE_DN_KS>::kTilesPerWG;
-  const int dn_wg = (p.H / 16 + dt - 1) / dt;
-  ffn_kernel<P, Proj::Down, MTMAX, AMOE_DN_NTW, AMOE_DN_KS, false, 8><<<dim3(cap * dn_wg), 256, 0, stream>>>(p);
   return hipGetLastError();
 }
 
@@ -1227,11 +898,22 @@ ColShape col_shape(int T, int H, int I, int is_bf16) {
   return c;
 }
 
-// blocks of up to 256 tokens and 2048 slots: gate/up builds its own dispatch,
-// the column-tile down pass replaces the per-slot pass and combine
-bool use_col_path(int T, int k) {
-  return T <= kColMaxT && T <= kSelfMaxT && static_cast<long long>(T) * k <= kColMaxSlots &&
-         static_cast<long long>(T) * k <= kSelfMaxSlots;
+// Column path (gate/up with its own dispatch, then the column-tile down pass)
+// or grouped path (dispatch, grouped GEMMs, combine).  The column path's lists
+// hold 256 tokens and 2048 slots; below that the line lies where the grouped
+// path's row reuse (both projections re-read an expert's rows once per 128
+// output rows instead of once per 32 or 16) outweighs its two more launches
+// and its slot rows.  Both FFN paths, us, column / grouped:
+//   H = 2048, I = 768:   T = 72 94 / 109, 96 111 / 114, 120 134 / 120, 240 224 / 189
+//   H = 4096, I = 1536:  T = 64 168 / 187, 96 277 / 270, 128 314 / 264
+//   fp32, H = 2048, I = 768 (fp32 products): T = 120 235 / 311, 240 410 / 373
+// A thin I leaves the grouped gate/up too few workgroups (one per 128 rows of
+// I and expert): H = 4096, I = 192, T = 120 89 / 102; I = 256 at T = 128 even.
+bool use_col_path(int T, int I, int k, int is_bf16) {
+  if (T > kColMaxT || T > kSelfMaxT || static_cast<long long>(T) * k > kColMaxSlots ||
+      static_cast<long long>(T) * k > kSelfMaxSlots)
+    return false;
+  return T <= (is_bf16 ? 96 : 192) || I < 256;
 }
 
 template <class P, int NB, int MTI>
@@ -1293,19 +975,26 @@ hipError_t launch_pack(const void* src, int is_bf16, int E, int N, int K, void* 
   return hipGetLastError();
 }
 
+// most items of the grouped path: one per active expert and one more per full item
+int grouped_max_items(int T, int E, int k, int is_bf16) {
+  const int slots = T * k;
+  return (E < slots ? E : slots) + slots / grouped_item_rows(is_bf16);
+}
+
 // workspace: [cnt E | off E+1 | active E | n_active | n_items] ints, CSR slot
-// ids, activations, then the per-slot output rows (row pass) or the down
-// items (column-tile pass)
+// ids, activations, then the items of the grouped GEMMs and the per-slot
+// output rows (grouped path) or the down items (column-tile path)
 size_t forward_workspace_bytes(int T, int H, int I, int E, int k, int is_bf16) {
   const size_t slots = static_cast<size_t>(T) * k;
   const size_t eb = is_bf16 ? 2 : 4;
   const size_t head = align256(sizeof(int32_t) * (3 * static_cast<size_t>(E) + 3)) +
                       align256(sizeof(int32_t) * slots) + align256(slots * I * eb);
-  if (use_col_path(T, k)) {
+  if (use_col_path(T, I, k, is_bf16)) {
     const size_t items = (slots + 15) / 16 + (static_cast<size_t>(E) < slots ? E : slots);
     return head + align256(items * sizeof(int4));
   }
-  return head + align256(slots * H * sizeof(float));
+  return head + align256(static_cast<size_t>(grouped_max_items(T, E, k, is_bf16)) * sizeof(int4)) +
+         align256(slots * H * sizeof(float));
 }
 
 void forward_carve(void* ws, ForwardParams& p) {
@@ -1323,43 +1012,43 @@ void forward_carve(void* ws, ForwardParams& p) {
   c += align256(sizeof(int32_t) * slots);
   p.act = c;
   c += align256(slots * p.I * eb);
-  if (use_col_path(p.T, p.k)) {
+  if (use_col_path(p.T, p.I, p.k, p.is_bf16)) {
     p.items = reinterpret_cast<int4*>(c);
     p.ys = nullptr;
   } else {
-    p.items = nullptr;
+    p.items = reinterpret_cast<int4*>(c);
+    c += align256(static_cast<size_t>(grouped_max_items(p.T, p.E, p.k, p.is_bf16)) * sizeof(int4));
     p.ys = reinterpret_cast<float*>(c);
   }
 }
 
 hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
-  const bool col = use_col_path(p.T, p.k);
-  const ColShape cs = col_shape(p.T, p.H, p.I, p.is_bf16);
-  p.zero_out = col && cs.ksplit == 2;
-  p.item_rows = 16 * cs.mti;
   const bool small_k = p.k <= 8;
   hipError_t err = hipSuccess;
-  if (!col) {
-    if (small_k)
-      dispatch_kernel<8><<<1, kDispatchThreads, 0, stream>>>(p);
+  if (use_col_path(p.T, p.I, p.k, p.is_bf16)) {
+    const ColShape cs = col_shape(p.T, p.H, p.I, p.is_bf16);
+    p.zero_out = cs.ksplit == 2;
+    p.item_rows = 16 * cs.mti;
+    // upper bound on active experts: min(E, T*k)
+    const int cap = p.E < p.T * p.k ? p.E : p.T * p.k;
+    const bool small_t = p.T <= 32;
+    if (p.is_bf16)
+      err = small_t ? launch_gate_up<Bf16Path, 2>(p, cap, stream) : launch_gate_up<Bf16Path, 4>(p, cap, stream);
     else
-      dispatch_kernel<kMaxTopK><<<1, kDispatchThreads, 0, stream>>>(p);
-    err = hipGetLastError();
+      err = small_t ? launch_gate_up<F32Path, 2>(p, cap, stream) : launch_gate_up<F32Path, 4>(p, cap, stream);
     if (err != hipSuccess) return err;
+    return p.is_bf16 ? launch_down_col<Bf16Path>(p, cs, stream) : launch_down_col<F32Path>(p, cs, stream);
   }
-  // upper bound on active experts: min(E, T*k)
-  const int cap = p.E < p.T * p.k ? p.E : p.T * p.k;
-  const bool small_t = p.T <= 32;
-  if (p.is_bf16)
-    err = small_t ? launch_gate_up<Bf16Path, 2>(p, cap, col, stream) : launch_gate_up<Bf16Path, 4>(p, cap, col, stream);
+  p.item_rows = grouped_item_rows(p.is_bf16);
+  p.big_rows = grouped_big_rows(p.is_bf16);
+  const int chunks = (p.T + kDispatchChunk - 1) / kDispatchChunk;
+  if (small_k)
+    dispatch_kernel<8><<<chunks, kDispatchThreads, 0, stream>>>(p);
   else
-    err = small_t ? launch_gate_up<F32Path, 2>(p, cap, col, stream) : launch_gate_up<F32Path, 4>(p, cap, col, stream);
+    dispatch_kernel<kMaxTopK><<<chunks, kDispatchThreads, 0, stream>>>(p);
+  err = hipGetLastError();
   if (err != hipSuccess) return err;
-  if (col) return p.is_bf16 ? launch_down_col<Bf16Path>(p, cs, stream) : launch_down_col<F32Path>(p, cs, stream);
-  if (p.is_bf16)
-    err = small_t ? launch_down_rows<Bf16Path, 2>(p, cap, stream) : launch_down_rows<Bf16Path, 4>(p, cap, stream);
-  else
-    err = small_t ? launch_down_rows<F32Path, 2>(p, cap, stream) : launch_down_rows<F32Path, 4>(p, cap, stream);
+  err = launch_grouped(p, grouped_max_items(p.T, p.E, p.k, p.is_bf16), stream);
   if (err != hipSuccess) return err;
   const int hblocks = (p.H / 4 + 255) / 256;
   const dim3 cgrid(static_cast<unsigned>(hblocks) * static_cast<unsigned>(p.T));

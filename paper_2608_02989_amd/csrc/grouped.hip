@@ -1,0 +1,356 @@
+// Grouped expert GEMMs for larger blocks: gate/up with SwiGLU, and down into
+// gate-scaled slot rows.
+//
+// A workgroup of 4 waves takes one item (expert, up to 192 of its dispatched
+// rows) and one run of output tiles.  Each wave streams the weights of its own
+// tiles straight into registers (4 fragments per K chunk: a gate/up tile pair,
+// or four 16-column tiles of the down projection); the item's rows are staged
+// in LDS, once for the four waves, and every fragment read from there meets
+// four weight fragments.  The rows are fetched once per 128 rows of I (256
+// columns of H).
+//
+// What bounds it: the weight stream at 15 to 60 tokens per expert (8 trees x
+// 64 nodes, H = 4096, I = 1536: gate/up streams 3.0 GB in 480 us = 6.3 TB/s,
+// 0.9 of a plain read; replacing the products by an XOR or the row gathers by
+// one row changed nothing), the weight stream and the work per stage together
+// at 120 (32 x 60 nodes, H = 2048, I = 768: 215 us, 128 us with weights from
+// L2).  Against the passes before it (K split over the waves, rows gathered by
+// every wave): gate/up 611 -> 480 and down 363 -> 280 us on the wide layer,
+// 412 -> 215 and 289 -> 127 us at 32 x 60.  No better, same shapes: two tiles
+// per wave at three workgroups per CU (482 / 240 us gate/up), four weight
+// stages in flight (484 / 223), K split two ways (486 / 245) or four ways
+// (533 / 376), two M groups for every item (615 / 248).
+#include <type_traits>
+
+#include "ffn_common.hpp"
+
+namespace amoe {
+
+namespace {
+
+constexpr int kGrpStage = 2;  // K chunks per LDS stage (128 bytes of each row)
+constexpr int kGrpFrags = 4;  // weight fragments per wave and K chunk
+
+enum class Grouped { GateUp, Down };
+
+// M-tiles per wave: the accumulators of 8 M-tiles x 4 fragments are half of
+// the registers two workgroups per CU leave a wave.  With two M groups each
+// thread also holds twice the rows in flight: 6.  The fp32 path keeps a second
+// accumulator set (below): 3.
+template <class P>
+constexpr int kGrpTileM = P::kElemBytes == 2 ? 8 : 2;
+template <class P>
+constexpr int kGrpTileM2 = P::kElemBytes == 2 ? 6 : 2;
+template <class P>
+constexpr int kGrpMaxRows = 2 * 16 * kGrpTileM2<P>;  // rows of an item
+
+// Adds the products of `rows` rows of one item into acc and returns with the
+// workgroup's LDS free.  w[f] / wbytes[f]: run of weight fragment f (a run of
+// 0 bytes reads as zeros and costs no traffic); chunk c of it sits wstride
+// 16-byte pieces after chunk c - 1.
+//
+// Stage i (kGrpStage chunks): the rows of stage i + 1, loaded one stage
+// earlier, go to the other LDS buffer, then the loads of the rows of stage
+// i + 2 and of the weights of stage i + 1 are issued, then stage i is
+// multiplied.  The row loads are issued before the weights of the same
+// round, so waiting for them leaves the weight stream in flight.
+template <class P, int MT, int MG>
+__device__ __forceinline__ void grouped_product(const uint4* const (&w)[kGrpFrags], const int (&wbytes)[kGrpFrags],
+                                                int wstride, const uint4* const (&xrow)[(MG * MT + 1) / 2], int KC,
+                                                int mt0, uint4* lds, floatx4 (&acc)[kGrpFrags][MT]) {
+  constexpr int kLoads = (MG * MT + 1) / 2;   // 16-byte row pieces per thread and stage
+  constexpr int kChunk = 2 * kLoads * kWave;  // pieces of one chunk of the item's rows in LDS
+  constexpr int kBuf = kGrpStage * kChunk;
+  const int tid = threadIdx.x, lane = lane_id();
+  const int r = lane & 15, g = lane >> 4;
+  // thread tid loads piece tid % 8 of rows tid / 8 + 32 s; a row's pieces of
+  // one stage fill two fragments.  Row r of a fragment's piece group sits at
+  // r ^ 2 * piece, so the eight pieces of a row fall into different banks.
+  const int piece = tid & 7;
+  const int srow = tid >> 3;
+  const int dst = (piece >> 2) * kChunk + (srow >> 4) * kWave + (piece & 3) * 16 + ((srow & 15) ^ (2 * piece));
+  const int src0 = g * 16 + (r ^ (2 * g));
+  const int src1 = g * 16 + (r ^ (2 * (g + 4)));
+  const int nst = (KC + kGrpStage - 1) / kGrpStage;
+  uint4 ra[kLoads];
+  uint4 wb[2][kGrpStage][kGrpFrags];
+  auto load_rows = [&](int st) {
+    const int kc = min(min(st, nst - 1) * kGrpStage + (piece >> 2), KC - 1);  // in range; see store_rows
+#pragma unroll
+    for (int s = 0; s < kLoads; ++s) ra[s] = xrow[s][kc * 4 + (piece & 3)];
+  };
+  auto store_rows = [&](int st, int buf) {
+    const bool in = st * kGrpStage + (piece >> 2) < KC;  // past the last chunk: zeros
+#pragma unroll
+    for (int s = 0; s < kLoads; ++s) lds[buf * kBuf + s * 2 * kWave + dst] = in ? ra[s] : make_uint4(0u, 0u, 0u, 0u);
+  };
+  auto load_w = [&](int st, uint4 (&v)[kGrpStage][kGrpFrags]) {
+#pragma unroll
+    for (int u = 0; u < kGrpStage; ++u)
+#pragma unroll
+      for (int f = 0; f < kGrpFrags; ++f)
+        v[u][f] = load_weight<MG == 1 ? kPolicyStream : kPolicyPlain>(w[f], wbytes[f], (st * kGrpStage + u) * wstride + lane);
+  };
+  auto multiply = [&](int buf, const uint4 (&v)[kGrpStage][kGrpFrags], floatx4 (&a)[kGrpFrags][MT]) {
+#pragma unroll
+    for (int u = 0; u < kGrpStage; ++u) {
+      uint4 x[MT];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) x[mt] = lds[buf * kBuf + u * kChunk + (mt0 + mt) * kWave + (u ? src1 : src0)];
+#pragma unroll
+      for (int f = 0; f < kGrpFrags; ++f)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) a[f][mt] = P::mma(x[mt], v[u][f], a[f][mt]);
+    }
+  };
+  load_rows(0);
+  load_w(0, wb[0]);
+  store_rows(0, 0);
+  load_rows(1);
+  __syncthreads();
+  auto stage = [&](int i, auto cur, floatx4 (&a)[kGrpFrags][MT]) {
+    constexpr int c = decltype(cur)::value;
+    store_rows(i + 1, c ^ 1);
+    load_rows(i + 2);
+    load_w(i + 1, wb[c ^ 1]);
+    __builtin_amdgcn_sched_barrier(0);  // the loads above stay above the products
+    multiply(c, wb[c], a);
+    __syncthreads();
+  };
+  if constexpr (P::kElemBytes == 4) {
+    // fp32 products: sums of 16 chunks, then the sums (shorter chains of
+    // roundings than one running sum over K)
+    constexpr int kFlush = 8;  // stages
+    floatx4 part[kGrpFrags][MT];
+#pragma unroll
+    for (int f = 0; f < kGrpFrags; ++f)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) part[f][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto flush = [&]() {
+#pragma unroll
+      for (int f = 0; f < kGrpFrags; ++f)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            acc[f][mt][q] += part[f][mt][q];
+            part[f][mt][q] = 0.f;
+          }
+    };
+    for (int i = 0;;) {
+      stage(i, std::integral_constant<int, 0>{}, part);
+      if (++i == nst) break;
+      stage(i, std::integral_constant<int, 1>{}, part);
+      if (i % kFlush == kFlush - 1) flush();
+      if (++i == nst) break;
+    }
+    flush();
+  } else {
+    for (int i = 0;;) {
+      stage(i, std::integral_constant<int, 0>{}, acc);
+      if (++i == nst) break;
+      stage(i, std::integral_constant<int, 1>{}, acc);
+      if (++i == nst) break;
+    }
+  }
+}
+
+template <class P>
+struct GroupedRows {  // an item's slots and their gates
+  int slot[kGrpMaxRows<P>];
+  float gate[kGrpMaxRows<P>];
+};
+
+// 16-byte pieces of LDS: two stages of an item's rows (M-tiles rounded up to
+// an even number, see grouped_product)
+template <class P>
+constexpr int kGrpLds = 2 * kGrpStage * (2 * kGrpTileM2<P> + 1) / 2 * 2 * kWave;
+
+// MT M-tiles per wave; MG = 2: the item has 2 MT M-tiles and the four waves
+// are two M groups over half as many output tiles.
+template <class P, Grouped F, int MT, int MG>
+__device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int row0, int rows, int nblk, uint4* lds,
+                                             GroupedRows<P>& gr) {
+  constexpr int kLoads = (MG * MT + 1) / 2;
+  constexpr int kTiles = F == Grouped::GateUp ? 2 : 4;  // output tiles per wave
+  int tid = threadIdx.x;
+  // opaque per instantiation: the compiler otherwise hoists the address
+  // arithmetic of every M-tile count above the branch between them and spills
+  asm volatile("" : "+v"(tid), "+s"(row0), "+s"(rows));
+  const int wave = wave_id(), lane = lane_id();
+  const int r = lane & 15, g = lane >> 4;
+  const int K = F == Grouped::GateUp ? p.H : p.I;
+  const int KC = K / P::kKF;
+  const int rowq = K * P::kElemBytes / 16;
+  const int ntiles = (F == Grouped::GateUp ? p.I : p.H) / 16;
+  const int mt0 = MG == 1 ? 0 : (wave & 1) * MT;  // this wave's first M-tile
+  const int tile0 = (nblk * (4 / MG) + wave / MG) * kTiles;
+
+  const uint4* w[kGrpFrags];
+  int wbytes[kGrpFrags];
+  int wstride;
+  if (F == Grouped::GateUp) {
+    const int npairs = (ntiles + 1) / 2, pair = tile0 / 2;
+    const bool in = pair < npairs;
+    const uint4* base = uniform_ptr(static_cast<const uint4*>(p.w_gate_up) +
+                                    (static_cast<size_t>(e) * npairs + (in ? pair : 0)) * KC * 4 * kWave);
+    wstride = 4 * kWave;
+    // fragments gate 2p, gate 2p + 1, up 2p, up 2p + 1 of a chunk lie side by side
+#pragma unroll
+    for (int f = 0; f < kGrpFrags; ++f) {
+      w[f] = base + f * kWave;
+      wbytes[f] = in ? (KC * 4 - f) * kWave * 16 : 0;
+    }
+  } else {
+    wstride = kWave;
+#pragma unroll
+    for (int f = 0; f < kGrpFrags; ++f) {
+      const bool in = tile0 + f < ntiles;
+      w[f] = uniform_ptr(static_cast<const uint4*>(p.w_down) +
+                         (static_cast<size_t>(e) * ntiles + (in ? tile0 + f : 0)) * KC * kWave);
+      wbytes[f] = in ? KC * kWave * 16 : 0;
+    }
+  }
+  // rows past the item's last read its first row; their outputs are dropped
+  const uint4* xrow[kLoads];
+#pragma unroll
+  for (int s = 0; s < kLoads; ++s) {
+    const int m = (tid >> 3) + 32 * s;
+    const int row = row0 + (m < rows ? m : 0);
+    xrow[s] = F == Grouped::GateUp
+                  ? static_cast<const uint4*>(p.hidden) + static_cast<size_t>(p.ent_slot[row] / p.k) * rowq
+                  : static_cast<const uint4*>(p.act) + static_cast<size_t>(row) * rowq;
+  }
+  if (F == Grouped::Down && tid < rows) {
+    const int slot = p.ent_slot[row0 + tid];
+    gr.slot[tid] = slot;
+    gr.gate[tid] = p.topk_gate[slot];
+  }
+  floatx4 acc[kGrpFrags][MT];
+#pragma unroll
+  for (int f = 0; f < kGrpFrags; ++f)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[f][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  grouped_product<P, MT, MG>(w, wbytes, wstride, xrow, KC, mt0, lds, acc);
+
+  // Lane (r, g) holds rows 4g .. 4g + 3 of column r of each tile.  Each M-tile
+  // goes through this wave's part of the LDS, so the rows leave in 16-byte
+  // pieces, whole 256 bytes (down) or 64 / 128 bytes (gate/up) per row (down
+  // at 32 x 60 nodes 173 -> 135 us against one 4-byte store per value).
+  constexpr int kOutEb = F == Grouped::GateUp ? P::kElemBytes : 4;
+  constexpr int kRowPieces = kTiles * kOutEb;           // 16-byte pieces per row
+  constexpr int kRowStride = kRowPieces * 16 + 16;      // bytes, padded
+  constexpr int kRowsPerStore = kWave / kRowPieces;
+  static_assert(16 * kRowStride * 4 <= kGrpLds<P> * 16, "one M-tile per wave fits");
+  char* mine = reinterpret_cast<char*>(lds) + wave * 16 * kRowStride;
+  const int nt = min(kTiles, ntiles - tile0);  // valid tiles of this wave (may be <= 0)
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int m0 = (mt0 + mt) * 16;
+    if (m0 >= rows) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      char* row = mine + (4 * g + i) * kRowStride + r * kOutEb;
+      if (F == Grouped::GateUp) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float v = silu_mul(acc[j][mt][i], acc[2 + j][mt][i]);
+          if (P::kElemBytes == 2)
+            *reinterpret_cast<uint16_t*>(row + 16 * j * kOutEb) = float_to_bf16_bits(v);
+          else
+            *reinterpret_cast<float*>(row + 16 * j * kOutEb) = v;
+        }
+      } else {
+        const float gate = gr.gate[min(m0 + 4 * g + i, rows - 1)];
+#pragma unroll
+        for (int f = 0; f < kGrpFrags; ++f) *reinterpret_cast<float*>(row + 16 * f * kOutEb) = gate * acc[f][mt][i];
+      }
+    }
+    wave_lds_sync();
+    const int pc = lane % kRowPieces;
+#pragma unroll
+    for (int q = 0; q < 16 / kRowsPerStore; ++q) {
+      const int lr = q * kRowsPerStore + lane / kRowPieces;
+      const int m = m0 + lr;
+      const uint4 v = *reinterpret_cast<const uint4*>(mine + lr * kRowStride + pc * 16);
+      if (m < rows && pc < nt * kOutEb) {
+        if (F == Grouped::GateUp)
+          reinterpret_cast<uint4*>(static_cast<char*>(p.act) +
+                                   (static_cast<size_t>(row0 + m) * p.I + tile0 * 16) * kOutEb)[pc] = v;
+        else
+          reinterpret_cast<uint4*>(p.ys + static_cast<size_t>(gr.slot[m]) * p.H + tile0 * 16)[pc] = v;
+      }
+    }
+    wave_lds_sync();
+  }
+}
+
+// Items come in groups of the workgroups that share one item's rows, group
+// after group round-robin over the XCDs (workgroup b runs on XCD b % 8), so
+// the rows are read from one XCD's L2.  An item of more than kGrpTileM M-tiles
+// runs two M groups over each half of its run in turn, so its weights still
+// come from HBM once; those loads use the default cache policy (the second M
+// group reads the same lines: 229 -> 215 us at 32 x 60 nodes), all others are
+// non-temporal (478 against 530 us on the wide layer).  Every item has the
+// same number of workgroups: workgroups that left at once held back the
+// dispatch of the other XCDs (428 of 512 resident).
+template <class P, Grouped F>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void grouped_kernel(ForwardParams p,
+                                                                                              int nblocks) {
+  __shared__ uint4 lds[kGrpLds<P>];
+  __shared__ GroupedRows<P> gr;
+  const int slot = blockIdx.x / 8;
+  const int item = (slot / nblocks) * 8 + blockIdx.x % 8, nblk = slot % nblocks;
+  if (item >= *p.n_items) return;
+  const int4 d = p.items[item];
+  const int e = __builtin_amdgcn_readfirstlane(d.x);
+  const int row0 = __builtin_amdgcn_readfirstlane(d.y);
+  const int rows = __builtin_amdgcn_readfirstlane(d.z);
+  const int mt = (rows + 15) / 16;
+  if (mt <= kGrpTileM<P>) {
+    if (mt == 1) grouped_item<P, F, 1, 1>(p, e, row0, rows, nblk, lds, gr);
+    else if (kGrpTileM<P> == 2 || mt == 2) grouped_item<P, F, 2, 1>(p, e, row0, rows, nblk, lds, gr);
+    else if constexpr (kGrpTileM<P> > 2) {
+      if (mt == 3) grouped_item<P, F, 3, 1>(p, e, row0, rows, nblk, lds, gr);
+      else if (mt == 4) grouped_item<P, F, 4, 1>(p, e, row0, rows, nblk, lds, gr);
+      else if (mt <= 6) grouped_item<P, F, 6, 1>(p, e, row0, rows, nblk, lds, gr);
+      else grouped_item<P, F, 8, 1>(p, e, row0, rows, nblk, lds, gr);
+    }
+  } else {
+    for (int h = 0; h < 2; ++h) {  // the two halves of the run
+      if constexpr (kGrpTileM<P> > 2) {
+        if (mt <= 10) grouped_item<P, F, 5, 2>(p, e, row0, rows, 2 * nblk + h, lds, gr);
+        else grouped_item<P, F, 6, 2>(p, e, row0, rows, 2 * nblk + h, lds, gr);
+      } else {
+        grouped_item<P, F, 2, 2>(p, e, row0, rows, 2 * nblk + h, lds, gr);
+      }
+      __syncthreads();  // the LDS parts of the waves are staging space again
+    }
+  }
+}
+
+template <class P>
+hipError_t launch_grouped_path(const ForwardParams& p, int max_items, hipStream_t stream) {
+  const int groups = (max_items + 7) / 8 * 8;
+  const int gu = (p.I / 16 + 7) / 8, dn = (p.H / 16 + 15) / 16;
+  // far beyond what the slot rows of one device's memory allow
+  if (static_cast<long long>(groups) * (gu > dn ? gu : dn) > 0x7fffffffll) return hipErrorInvalidValue;
+  grouped_kernel<P, Grouped::GateUp><<<groups * gu, 256, 0, stream>>>(p, gu);
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  grouped_kernel<P, Grouped::Down><<<groups * dn, 256, 0, stream>>>(p, dn);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+int grouped_item_rows(int is_bf16) { return is_bf16 ? kGrpMaxRows<Bf16Path> : kGrpMaxRows<F32Path>; }
+
+int grouped_big_rows(int is_bf16) { return 16 * (is_bf16 ? kGrpTileM<Bf16Path> : kGrpTileM<F32Path>); }
+
+hipError_t launch_grouped(const ForwardParams& p, int max_items, hipStream_t stream) {
+  return p.is_bf16 ? launch_grouped_path<Bf16Path>(p, max_items, stream)
+                   : launch_grouped_path<F32Path>(p, max_items, stream);
+}
+
+}  // namespace amoe

@@ -82,13 +82,19 @@ struct ForwardParams {
   int32_t* n_active;  // [1]
   int32_t* ent_slot;  // [T * k] slot ids grouped by expert, token order
   void* act;          // [T * k, I] bf16 or fp32
-  float* ys;          // [T * k, H] gate-weighted expert outputs (per-slot down pass only)
-  int4* items;        // down-pass work items (e, first CSR row, rows) (column-tile pass only)
+  float* ys;          // [T * k, H] gate-weighted expert outputs (grouped path only)
+  int4* items;        // work items (e, first CSR row, rows): column-tile down pass or grouped GEMMs
   int32_t* n_items;   // [1]
   int T, H, I, E, k, is_bf16;
   int zero_out;       // gate/up pass clears out (the down pass then adds two halves into it)
-  int item_rows;      // tokens per column-tile down item (16 per M-tile)
+  int item_rows;      // most rows of an item (16 per M-tile)
+  int big_rows;       // items of the grouped GEMMs above this size take two M groups
 };
+
+// grouped GEMMs of larger blocks (grouped.hip): rows per item, rows per M group, and both passes
+int grouped_item_rows(int is_bf16);
+int grouped_big_rows(int is_bf16);
+hipError_t launch_grouped(const ForwardParams& p, int max_items, hipStream_t stream);
 
 size_t forward_workspace_bytes(int T, int H, int I, int E, int k, int is_bf16);
 void forward_carve(void* ws, ForwardParams& p);

@@ -436,6 +436,29 @@ def test_forward_parity_m_groups(gpu, dtype):
 
 # one GPU's share of a tensor-parallel split over I: thin I gives the column-tile
 # down pass 3-step stages (one column tile at H = 1024, two at H = 4096)
+# Grouped GEMMs (blocks beyond the in-workgroup dispatch): experts at the edges
+# of the M-tiles per wave (bf16: 1, 2, 3, 4, 6, 8), of the two M groups
+# (10 and 12 M-tiles together; fp32: above 32 rows) and of an item (192 rows;
+# fp32: 64), K chunks that do not fill the last LDS stage (H = 160, I = 96:
+# 5 and 3 bf16 chunks) and output runs that end inside a workgroup's share.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,counts", [(400, [1, 16, 17, 48, 49, 64, 96, 97]),
+                                      (515, [112, 128, 129, 160, 161, 192, 193, 400, 15, 32, 33, 65])])
+def test_forward_parity_grouped_edges(gpu, dtype, T, counts):
+    E, k = len(counts) + 1, len(counts)
+    cfg = W.LayerConfig("grouped", 960 + T, dtype, T=T, B=1, H=160, E=E, k=k, I=96, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    rng = np.random.default_rng(T)
+    h32 = rng.standard_normal((T, cfg.H)).astype(np.float32)
+    gate = rng.random((T, k)).astype(np.float32)
+    idx = np.full((T, k), -1, np.int32)  # expert 0 stays without tokens
+    for j, n in enumerate(counts):
+        idx[rng.permutation(T)[:n], j] = j + 1
+    got, h64, (wg, wu, wd) = forward_case(cfg, idx, gate, h32)
+    ref = O.moe_forward_grouped(h64, wg, wu, wd, idx, np.where(idx < 0, 0.0, gate).astype(np.float32), cfg.dtype)
+    check_forward(got, ref, cfg.dtype, f"grouped edges T={T} {dtype}")
+
+
 @pytest.mark.parametrize("H,I,T,E", [(1024, 96, 32, 64), (4096, 192, 64, 32)])
 def test_forward_parity_thin_shard(gpu, H, I, T, E):
     cfg = W.LayerConfig("thin", 96 + I, "bf16", T=T, B=1, H=H, E=E, k=8, I=I, depth_max=6,
