@@ -493,7 +493,7 @@ __device__ __forceinline__ void gate_up_pass(const ForwardParams& p, const int32
   }
 }
 
-// the full CSR is built only by the publishing workgroup, after its items
+// the full CSR is built only by the publishing workgroup
 template <int KMAX>
 union DispatchSlot {
   SelfDispatch sd;
@@ -510,10 +510,11 @@ union DispatchSlot {
 // of H = 2048 (256 KiB) do not repay the prologue each extra workgroup
 // repeats: the 48-layer pass at T = 60 ran 4951, 4990 and 5054 us per block
 // with one, two and three times the resident grid.  Workgroups left without
-// an item exit after the prologue.  Workgroup 0, which is dispatched first
-// and has the most items, builds the full CSR afterwards and publishes it for
-// the down pass.  (Claiming items from a device-wide counter was measured no
-// better.)
+// an item exit after the prologue.  Workgroup 0 takes no item: it builds the
+// full CSR and publishes it for the down pass, beside the others' streams
+// (after an item of its own that work ended 2-3 us behind every other
+// workgroup: one token's gate/up pass 12.8 us, of it 10.4 for the items).
+// (Claiming items from a device-wide counter was measured no better.)
 constexpr int kSelfGridMult = 3;
 
 // Occupancy floor: three workgroups per CU for up to two M-tiles, two for
@@ -542,8 +543,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MTMAX <= 2 
       else gate_up_pass<P, MTMAX>(p, ent_e, e, tile0, n_e, o_e, m0, red);
     }
   };
-  ItemDispatch<KMAX>& id = ds.id;
   const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
+  if (blockIdx.x == 0) {
+    SelfDispatch& sd = ds.sd;
+    self_dispatch<KMAX>(p, sd, tid);
+    publish_dispatch(p, sd, tid);
+    return;
+  }
+  ItemDispatch<KMAX>& id = ds.id;
   const int T = p.T, k = p.k, E = p.E, words = (E + 31) / 32;
   if (tid < kMaxExperts / 32) id.emask[tid] = 0u;
   {
@@ -569,7 +576,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MTMAX <= 2 
   for (int w = 0; w < words; ++w) nact += __popc(id.emask[w]);
   nact = __builtin_amdgcn_readfirstlane(nact);
   const int n_items = nact * wg_per_expert;
-  for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+  for (int item = blockIdx.x - 1; item < n_items; item += gridDim.x - 1) {
     const int e = __builtin_amdgcn_readfirstlane(nth_set_bit(id.emask, words, item / wg_per_expert));
     // this thread's token: its slot of e, and its slots of lower experts
     int slot = -1, less = 0;
@@ -603,12 +610,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MTMAX <= 2 
     __syncthreads();
     run_expert((item % wg_per_expert) * kTilesPerWG, e, __builtin_amdgcn_readfirstlane(n_e),
                __builtin_amdgcn_readfirstlane(o_e), id.ent);
-  }
-  if (blockIdx.x == 0) {
-    __syncthreads();  // the per-item state shares this LDS
-    SelfDispatch& sd = ds.sd;
-    self_dispatch<KMAX>(p, sd, tid);
-    publish_dispatch(p, sd, tid);
   }
 }
 
@@ -840,17 +841,24 @@ int resident_workgroups() {
   return cached[dev];
 }
 
+// Rows of 9 to 16 slots have an instantiation of their own: the search for
+// repeated experts grows with the square of the row (512 experts, top-10,
+// T = 64: 9.7 us before the first weight with rows of 32, pass 93.5 -> 82.7 us).
 template <class P, int MTMAX>
 hipError_t launch_gate_up(const ForwardParams& p, int cap, hipStream_t stream) {
   const int items = cap * ((p.I / 16 + kTilesPerWG - 1) / kTilesPerWG);
   if (p.k <= 8) {
     constexpr auto kern = &gate_up_kernel<P, MTMAX, 8>;
     const int res = (p.H >= 4096 ? kSelfGridMult : 1) * resident_workgroups<kern>();
-    kern<<<dim3(items < res ? items : res), 256, 0, stream>>>(p);
+    kern<<<dim3((items < res ? items : res) + 1), 256, 0, stream>>>(p);
+  } else if (p.k <= 16) {
+    constexpr auto kern = &gate_up_kernel<P, MTMAX, 16>;
+    const int res = (p.H >= 4096 ? kSelfGridMult : 1) * resident_workgroups<kern>();
+    kern<<<dim3((items < res ? items : res) + 1), 256, 0, stream>>>(p);
   } else {
     constexpr auto kern = &gate_up_kernel<P, MTMAX, kMaxTopK>;
     const int res = (p.H >= 4096 ? kSelfGridMult : 1) * resident_workgroups<kern>();
-    kern<<<dim3(items < res ? items : res), 256, 0, stream>>>(p);
+    kern<<<dim3((items < res ? items : res) + 1), 256, 0, stream>>>(p);
   }
   return hipGetLastError();
 }
@@ -1023,7 +1031,6 @@ void forward_carve(void* ws, ForwardParams& p) {
 }
 
 hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
-  const bool small_k = p.k <= 8;
   hipError_t err = hipSuccess;
   if (use_col_path(p.T, p.I, p.k, p.is_bf16)) {
     const ColShape cs = col_shape(p.T, p.H, p.I, p.is_bf16);
@@ -1042,8 +1049,10 @@ hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
   p.item_rows = grouped_item_rows(p.is_bf16);
   p.big_rows = grouped_big_rows(p.is_bf16);
   const int chunks = (p.T + kDispatchChunk - 1) / kDispatchChunk;
-  if (small_k)
+  if (p.k <= 8)
     dispatch_kernel<8><<<chunks, kDispatchThreads, 0, stream>>>(p);
+  else if (p.k <= 16)
+    dispatch_kernel<16><<<chunks, kDispatchThreads, 0, stream>>>(p);
   else
     dispatch_kernel<kMaxTopK><<<chunks, kDispatchThreads, 0, stream>>>(p);
   err = hipGetLastError();
@@ -1052,8 +1061,10 @@ hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
   if (err != hipSuccess) return err;
   const int hblocks = (p.H / 4 + 255) / 256;
   const dim3 cgrid(static_cast<unsigned>(hblocks) * static_cast<unsigned>(p.T));
-  if (small_k)
+  if (p.k <= 8)
     combine_kernel<8><<<cgrid, 256, 0, stream>>>(p, hblocks);
+  else if (p.k <= 16)
+    combine_kernel<16><<<cgrid, 256, 0, stream>>>(p, hblocks);
   else
     combine_kernel<kMaxTopK><<<cgrid, 256, 0, stream>>>(p, hblocks);
   return hipGetLastError();

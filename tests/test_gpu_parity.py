@@ -436,6 +436,21 @@ def test_forward_parity_m_groups(gpu, dtype):
 
 # one GPU's share of a tensor-parallel split over I: thin I gives the column-tile
 # down pass 3-step stages (one column tile at H = 1024, two at H = 4096)
+# routing rows of 16 and 17 slots (the kernels hold rows of up to 8, 16 or 32)
+# on both FFN paths; one token alone takes workgroups without an item
+@pytest.mark.parametrize("T,k", [(1, 16), (20, 16), (20, 17), (300, 16), (300, 17)])
+def test_forward_parity_row_sizes(gpu, T, k):
+    cfg = W.LayerConfig("rows", 1200 + k, "bf16", T=T, B=1, H=128, E=40, k=k, I=96, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    rng = np.random.default_rng(T + k)
+    h32 = rng.standard_normal((T, cfg.H)).astype(np.float32)
+    idx = np.stack([rng.permutation(cfg.E)[:k] for _ in range(T)]).astype(np.int32)
+    gate = rng.random((T, k)).astype(np.float32)
+    got, h64, (wg, wu, wd) = forward_case(cfg, idx, gate, h32)
+    ref = O.moe_forward_grouped(h64, wg, wu, wd, idx, gate, cfg.dtype)
+    check_forward(got, ref, cfg.dtype, f"row sizes T={T} k={k}")
+
+
 # Grouped GEMMs (blocks beyond the in-workgroup dispatch): experts at the edges
 # of the M-tiles per wave (bf16: 1, 2, 3, 4, 6, 8), of the two M groups
 # (10 and 12 M-tiles together; fp32: above 32 rows) and of an item (192 rows;
