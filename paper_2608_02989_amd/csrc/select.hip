@@ -11,9 +11,10 @@
 //         residency pruning -> S'                        (Eq. 6, Sec. 3.3, Eq. 7)
 //   restricted top-k  per node: top-k over S' and renormalised gates   (Eq. 2)
 //
-// Three launches: natural_kernel and restricted_kernel put one wave on each
-// node and spread the nodes over many CUs; tree_kernel runs one 1024-thread
-// workgroup per tree between them.  The per-node top-k is bound by
+// Blocks of small trees take one launch (small_tree_kernel), others three:
+// natural_kernel and restricted_kernel put one wave on each node and spread
+// the nodes over many CUs; tree_kernel runs one 1024-thread workgroup per tree
+// between them.  The per-node top-k is bound by
 // instruction issue (a ballot search over the key bits, fp64 exponentials):
 // a block's nodes on one CU queue behind each other on its four SIMDs, which
 // costs more than the two launches saved by running everything in one
@@ -895,6 +896,55 @@ __global__ __launch_bounds__(kNodeWaves * kWave) void restricted_kernel(SelectPa
   }
 }
 
+// ---------------------------------------------------------------------------
+// all three stages of small trees, one workgroup per tree and one wave per
+// node: the natural entries stay in LDS and the logits in registers, and two
+// launches fall away.  See fused_select for where this pays.
+// ---------------------------------------------------------------------------
+constexpr int kFusedNodes = kSelThreads / kWave;  // one wave per node
+
+template <int EPL>
+__global__ __launch_bounds__(kSelThreads) void small_tree_kernel(SelectParams p, TreeOffsets offs) {
+  __shared__ SelShared sh;
+  __shared__ NodeSlot slots[kFusedNodes];
+  __shared__ int32_t kidx[kFusedNodes * kMaxTopK];
+  __shared__ double rr[kFusedNodes * kMaxTopK];
+  __shared__ uint32_t routed[kRoutedWords];
+  TreeCtx c = tree_ctx(offs, blockIdx.x);
+  const int k = p.k;
+  const bool node = c.wave < c.Tb;
+  const int t[1] = {c.t_begin + c.wave};
+  NodeSlot* const sl[1] = {&slots[c.wave]};
+  float zv[1][EPL];
+  if (node) load_row<EPL>(p.logits + static_cast<size_t>(t[0]) * p.E, p.E, c.lane, zv[0]);
+  tree_p1(sh, p, c);
+  if (c.tid < kRoutedWords) routed[c.tid] = 0u;
+  if (node)
+    natural_nodes<EPL, 1>(p, t, zv, c.lane, sl, [&](int, int slot, int e, double r) {
+      kidx[c.wave * k + slot] = e;
+      rr[c.wave * k + slot] = r;
+    });
+  __syncthreads();
+  const int code = tree_code(sh);
+  if (code != 0) {
+    tree_invalid(p, c, code);  // sh.inSp stays empty, so the nodes get no routing
+  } else {
+    tree_alpha(sh, p, c);
+    __syncthreads();
+    tree_p3<false>(sh, p, c, kidx, rr, 0, 0.0);
+    __syncthreads();
+    tree_p4<EPL>(sh, p, c);
+  }
+  const bool live[1] = {true};
+  if (node) restricted_nodes<EPL, 1>(p, t, live, zv, sh.inSp, c.lane, sl, routed);
+  if (p.stats == nullptr || code != 0) return;
+  __syncthreads();
+  if (c.wave == 0) {
+    const int n = wave_sum_i32(c.lane < kRoutedWords ? __popc(routed[c.lane]) : 0);
+    if (c.lane == 0) p.stats[c.b * kNumStats + 9] = n;
+  }
+}
+
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 }  // namespace
@@ -917,8 +967,28 @@ void select_carve(void* ws, int T, int E, int k, SelectParams& p) {
   p.ws_routed = reinterpret_cast<uint32_t*>(c);
 }
 
+// One launch for blocks of small trees, or three.  A CU works off a tree's
+// nodes four at a time, so the single launch wins while that queue is shorter
+// than two launches.  us, one / three launches (graph of selections):
+// E = 128, 1 node 7.6 / 10.2, 6 nodes 9.6 / 12.6, 16 nodes 11.4 / 12.8, 16
+// trees of 16 11.8 / 13.9; two nodes per wave 32 nodes 18.2 / 13.5.
+// E = 512, whose rows take four times the work: 8 nodes 14.8 / 18.8 (kernels
+// alone), 16 nodes 20.0 / 19.0.  The MoE-Spec mode needs whole softmax rows in
+// the workspace and stays with three.
+bool fused_select(const SelectParams& p, const TreeOffsets& offs) {
+  const int most = p.E <= 256 ? kFusedNodes : kFusedNodes / 2;
+  if (p.mode == MODE_MOESPEC) return false;
+  for (int b = 0; b < p.B; ++b)
+    if (offs.o[b + 1] - offs.o[b] > most) return false;
+  return true;
+}
+
 template <int EPL>
 hipError_t launch_select_epl(const SelectParams& p, const TreeOffsets& offs, hipStream_t stream) {
+  if (fused_select(p, offs)) {
+    small_tree_kernel<EPL><<<p.B, kSelThreads, 0, stream>>>(p, offs);
+    return hipGetLastError();
+  }
   const int node_blocks = (p.T + kNodeWaves - 1) / kNodeWaves;
   if (node_blocks > 0) natural_kernel<EPL><<<node_blocks, kNodeWaves * kWave, 0, stream>>>(p);
   tree_kernel<EPL><<<p.B, kSelThreads, 0, stream>>>(p, offs);

@@ -236,6 +236,49 @@ def test_select_parity_batch_with_invalid_trees(gpu, sizes):
     assert_select_equal(got, ref, "batch with invalid trees")
 
 
+# blocks whose trees all have at most 16 nodes (8 above 256 experts) run in one
+# launch: against the oracle, and bit for bit against the three launches, which
+# the same trees take when a larger tree follows them
+@pytest.mark.parametrize("E,k,sizes", [(128, 8, [16, 1, 0, 7, 16, 2]), (20, 20, [3, 16]), (64, 1, [1]), (256, 10, [9, 16]),
+                                       (512, 32, [8, 1, 5]), (300, 6, [8])])
+@pytest.mark.parametrize("mode,budget", [(L.MODE_SELF_SIZING, 0), (L.MODE_ALL_EXPERTS, 0), (L.MODE_FIXED_BUDGET, 24),
+                                         (L.MODE_MOESPEC, 24), (L.MODE_COUNT, 24)])
+def test_select_small_trees_match_general_path(gpu, E, k, sizes, mode, budget):
+    rng = np.random.default_rng(E + k)
+    budget = min(budget, E)
+
+    def block(sz):
+        pars, deps, probs, offs = [], [], [], [0]
+        r = np.random.default_rng(E)
+        for n in sz:
+            par, dep, sib = W.make_tree(r, n, 6) if n else (np.zeros(0, np.int32),) * 3
+            pars.append(np.where(par < 0, -1, par + offs[-1]))
+            deps.append(dep)
+            probs.append((0.75 ** dep * 0.6 ** sib).astype(np.float32))
+            offs.append(offs[-1] + n)
+        par, dep, prob = (np.concatenate(x) for x in (pars, deps, probs))
+        return par.astype(np.int32), dep.astype(np.int32), prob.astype(np.float32), offs
+
+    par, dep, prob, offs = block(sizes + [17])
+    z32 = rng.standard_normal((offs[-1], E)).astype(np.float32)
+    z32[0, : E // 2] = 0.25                       # ties at the root
+    if len(sizes) > 3:
+        par[offs[3] + 2] = offs[0]                # a parent in another tree
+    T, B = offs[-2], len(sizes)
+    for resident, beta in ((None, 0.5), ((rng.random(E) < 0.3).astype(np.uint8), 1.5)):
+        say(f"select small trees E={E} k={k} sizes={sizes} mode={mode} mask={resident is not None}")
+        got, ref = run_select_both(z32[:T], par[:T], dep[:T], prob[:T], offs[:-1], k, beta, mode, budget,
+                                   resident=resident)
+        big, _ = run_select_both(z32, par, dep, prob, offs, k, beta, mode, budget, resident=resident)
+        assert_select_equal(got, ref, "small trees")
+        for key, n in (("eligible", B), ("idx", T), ("gate", T), ("stats", B)):
+            assert np.array_equal(got[key][:n].view(np.uint8), big[key][:n].view(np.uint8)), key
+    if len(sizes) == 1:                            # chain, no parents; no statistics asked for
+        n = sizes[0]
+        got, ref = run_select_both(z32[:n], None, np.arange(n), prob[:n], None, k, 0.5, mode, budget, parent_none=True)
+        assert_select_equal(got, ref, "small chain")
+
+
 # the largest batch of trees: ACCEPTMOE_MAX_TREES ragged trees (empty ones
 # included), with a residency mask and in the fixed-budget mode
 @pytest.mark.parametrize("mode,budget", [(L.MODE_SELF_SIZING, 0), (L.MODE_FIXED_BUDGET, 12)])
