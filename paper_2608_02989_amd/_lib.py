@@ -45,10 +45,10 @@ SIGNATURES = {
     "acceptmoe_pack_router_weights": (_i32, [_vp, _i32, _i32, _vp, _vp]),
     "acceptmoe_route": (_i32, [_vp, _i32, _vp, _i32, _i32, _i32, _vp, _vp]),
     "acceptmoe_select_workspace_size": (_sz, [_i32, _i32, _i32]),
-    "acceptmoe_select": (_i32, [_vp, _vp, _vp, _vp, ctypes.POINTER(_i32), _i32, _i32, _i32, _i32,
+    "acceptmoe_select": (_i32, [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32,
                                 ctypes.c_double, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _sz,
                                 _vp]),
-    "acceptmoe_select_noalloc": (_i32, [_vp, _vp, _vp, _vp, ctypes.POINTER(_i32), _i32, _i32, _i32, _i32,
+    "acceptmoe_select_noalloc": (_i32, [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32,
                                         ctypes.c_double, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp]),
     "acceptmoe_packed_weights_bytes": (_sz, [_i32, _i32, _i32, _i32]),
     "acceptmoe_pack_expert_weights": (_i32, [_vp, _i32, _i32, _i32, _i32, _vp, _vp]),

@@ -675,6 +675,45 @@ def test_end_to_end(gpu, name, rho):
 # ---------------------------------------------------------------------------
 # HIP graph capture of a whole step: every replay equals the eager result
 # ---------------------------------------------------------------------------
+# VerifyLayer.step makes the three calls itself: the same bits as route(),
+# select() and moe_forward(), at the layer's full size and below it, on another
+# stream, and larger or mistyped blocks refused before anything is launched
+def test_step_matches_separate_calls(gpu):
+    cfg = W.LayerConfig("step", 88, "bf16", T=12, B=3, H=256, E=24, k=4, I=96, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    blk = W.make_block(cfg)
+    hdev, _ = hidden_for(cfg, blk.hidden)
+    wg, wu, wd = W.expert_weights_torch(cfg, 0, DEV)
+    layer = ops.VerifyLayer(f32(W.router_weights(cfg)), wg, wu, wd, cfg.k, max_tokens=36, max_trees=3, budget=9,
+                            mode=L.MODE_FIXED_BUDGET)
+    side = torch.cuda.Stream()
+    for B, stream in ((3, None), (1, None), (2, side)):
+        T = 12 * B
+        hid, par, dep, pr = (to_dev_hidden(cfg, hdev[:T]), i32(blk.parent[:T]), i32(blk.depth[:T]), f32(blk.prob[:T]))
+        offs = blk.offsets[:B + 1] if B > 1 else None
+        z = ops.route(hid, layer.router)
+        sel = ops.select(z, par, dep, pr, offs, cfg.k, 0.5, L.MODE_FIXED_BUDGET, 9)
+        y = ops.moe_forward(hid, layer.wgu, layer.wd, sel["idx"], sel["gate"])
+        torch.cuda.synchronize()
+        logits, outs, out = layer.step(hid, par, dep, pr, offs, stream=stream)
+        torch.cuda.synchronize()
+        assert logits.shape == z.shape and out.shape == y.shape
+        assert torch.equal(logits, z) and torch.equal(out, y)
+        for key in sel:
+            assert torch.equal(outs[key], sel[key]), key
+    hid, par, dep, pr = (to_dev_hidden(cfg, hdev), i32(blk.parent), i32(blk.depth), f32(blk.prob))
+    with pytest.raises(ValueError):
+        layer.step(torch.cat([hid, hid]), par, dep, pr)
+    with pytest.raises(ValueError):
+        layer.step(hid, par, dep, pr, [0, 9, 18, 27, 36])
+    with pytest.raises(ValueError):
+        layer.step(hid[:, :128].contiguous(), par, dep, pr)
+    with pytest.raises(TypeError):
+        layer.step(hid.float(), par, dep, pr)
+    with pytest.raises(TypeError):
+        layer.step(hid, par.long(), dep, pr)
+
+
 def test_graph_replay_matches_eager(gpu):
     cfg = W.CONFIGS["qwen3_30b_a3b"]
     rw = W.router_weights(cfg)
