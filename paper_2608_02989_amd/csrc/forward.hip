@@ -121,7 +121,8 @@ __device__ __forceinline__ void write_down_items(const ForwardParams& p, const i
 // Items (expert, first CSR row, rows) of the grouped GEMMs: each active
 // expert's rows in equal runs of whole M-tiles, at most p.item_rows rows each,
 // and their count (one wave).  Items of more than p.big_rows rows, which take
-// longest, come first, each group in active-expert order.
+// longest, come first (their count goes to n_active), each group in
+// active-expert order.
 __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, const int* cnt, const int* off,
                                                     const int* active, int na, int tid) {
   int base = 0;
@@ -139,6 +140,7 @@ __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, cons
         p.items[base + incl - nr + m] = make_int4(e, off[e] + per * m, min(per, c - per * m), 0);
       base += lane_value(incl, kWave - 1);
     }
+    if (big != 0 && tid == 0) *p.n_active = base;
   }
   if (tid == 0) *p.n_items = base;
 }

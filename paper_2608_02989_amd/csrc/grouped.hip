@@ -20,6 +20,7 @@
 // per wave at three workgroups per CU (482 / 240 us gate/up), four weight
 // stages in flight (484 / 223), K split two ways (486 / 245) or four ways
 // (533 / 376), two M groups for every item (615 / 248).
+#include <algorithm>
 #include <type_traits>
 
 #include "ffn_common.hpp"
@@ -29,7 +30,7 @@ namespace amoe {
 namespace {
 
 constexpr int kGrpStage = 2;  // K chunks per LDS stage (128 bytes of each row)
-constexpr int kGrpFrags = 4;  // weight fragments per wave and K chunk
+constexpr int kGrpFrags = 4;  // most weight fragments per wave and K chunk (2 in a half run)
 
 enum class Grouped { GateUp, Down };
 
@@ -54,10 +55,10 @@ constexpr int kGrpMaxRows = 2 * 16 * kGrpTileM2<P>;  // rows of an item
 // i + 2 and of the weights of stage i + 1 are issued, then stage i is
 // multiplied.  The row loads are issued before the weights of the same
 // round, so waiting for them leaves the weight stream in flight.
-template <class P, int MT, int MG>
-__device__ __forceinline__ void grouped_product(const uint4* const (&w)[kGrpFrags], const int (&wbytes)[kGrpFrags],
+template <class P, int MT, int MG, int FR>
+__device__ __forceinline__ void grouped_product(const uint4* const (&w)[FR], const int (&wbytes)[FR],
                                                 int wstride, const uint4* const (&xrow)[(MG * MT + 1) / 2], int KC,
-                                                int mt0, uint4* lds, floatx4 (&acc)[kGrpFrags][MT]) {
+                                                int mt0, uint4* lds, floatx4 (&acc)[FR][MT]) {
   constexpr int kLoads = (MG * MT + 1) / 2;   // 16-byte row pieces per thread and stage
   constexpr int kChunk = 2 * kLoads * kWave;  // pieces of one chunk of the item's rows in LDS
   constexpr int kBuf = kGrpStage * kChunk;
@@ -73,7 +74,7 @@ __device__ __forceinline__ void grouped_product(const uint4* const (&w)[kGrpFrag
   const int src1 = g * 16 + (r ^ (2 * (g + 4)));
   const int nst = (KC + kGrpStage - 1) / kGrpStage;
   uint4 ra[kLoads];
-  uint4 wb[2][kGrpStage][kGrpFrags];
+  uint4 wb[2][kGrpStage][FR];
   auto load_rows = [&](int st) {
     const int kc = min(min(st, nst - 1) * kGrpStage + (piece >> 2), KC - 1);  // in range; see store_rows
 #pragma unroll
@@ -84,21 +85,21 @@ __device__ __forceinline__ void grouped_product(const uint4* const (&w)[kGrpFrag
 #pragma unroll
     for (int s = 0; s < kLoads; ++s) lds[buf * kBuf + s * 2 * kWave + dst] = in ? ra[s] : make_uint4(0u, 0u, 0u, 0u);
   };
-  auto load_w = [&](int st, uint4 (&v)[kGrpStage][kGrpFrags]) {
+  auto load_w = [&](int st, uint4 (&v)[kGrpStage][FR]) {
 #pragma unroll
     for (int u = 0; u < kGrpStage; ++u)
 #pragma unroll
-      for (int f = 0; f < kGrpFrags; ++f)
+      for (int f = 0; f < FR; ++f)
         v[u][f] = load_weight<MG == 1 ? kPolicyStream : kPolicyPlain>(w[f], wbytes[f], (st * kGrpStage + u) * wstride + lane);
   };
-  auto multiply = [&](int buf, const uint4 (&v)[kGrpStage][kGrpFrags], floatx4 (&a)[kGrpFrags][MT]) {
+  auto multiply = [&](int buf, const uint4 (&v)[kGrpStage][FR], floatx4 (&a)[FR][MT]) {
 #pragma unroll
     for (int u = 0; u < kGrpStage; ++u) {
       uint4 x[MT];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) x[mt] = lds[buf * kBuf + u * kChunk + (mt0 + mt) * kWave + (u ? src1 : src0)];
 #pragma unroll
-      for (int f = 0; f < kGrpFrags; ++f)
+      for (int f = 0; f < FR; ++f)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) a[f][mt] = P::mma(x[mt], v[u][f], a[f][mt]);
     }
@@ -108,7 +109,7 @@ __device__ __forceinline__ void grouped_product(const uint4* const (&w)[kGrpFrag
   store_rows(0, 0);
   load_rows(1);
   __syncthreads();
-  auto stage = [&](int i, auto cur, floatx4 (&a)[kGrpFrags][MT]) {
+  auto stage = [&](int i, auto cur, floatx4 (&a)[FR][MT]) {
     constexpr int c = decltype(cur)::value;
     store_rows(i + 1, c ^ 1);
     load_rows(i + 2);
@@ -121,14 +122,14 @@ __device__ __forceinline__ void grouped_product(const uint4* const (&w)[kGrpFrag
     // fp32 products: sums of 16 chunks, then the sums (shorter chains of
     // roundings than one running sum over K)
     constexpr int kFlush = 8;  // stages
-    floatx4 part[kGrpFrags][MT];
+    floatx4 part[FR][MT];
 #pragma unroll
-    for (int f = 0; f < kGrpFrags; ++f)
+    for (int f = 0; f < FR; ++f)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) part[f][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
     auto flush = [&]() {
 #pragma unroll
-      for (int f = 0; f < kGrpFrags; ++f)
+      for (int f = 0; f < FR; ++f)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -166,13 +167,14 @@ struct GroupedRows {  // an item's slots and their gates
 template <class P>
 constexpr int kGrpLds = 2 * kGrpStage * (2 * kGrpTileM2<P> + 1) / 2 * 2 * kWave;
 
-// MT M-tiles per wave; MG = 2: the item has 2 MT M-tiles and the four waves
-// are two M groups over half as many output tiles.
-template <class P, Grouped F, int MT, int MG>
-__device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int row0, int rows, int nblk, uint4* lds,
+// MT M-tiles per wave, FR weight fragments.  MG = 2: the item has 2 MT M-tiles
+// and the four waves are two M groups over half as many output tiles.  MG = 2
+// or FR = 2: `run` counts half runs.
+template <class P, Grouped F, int MT, int MG, int FR>
+__device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int row0, int rows, int run, uint4* lds,
                                              GroupedRows<P>& gr) {
   constexpr int kLoads = (MG * MT + 1) / 2;
-  constexpr int kTiles = F == Grouped::GateUp ? 2 : 4;  // output tiles per wave
+  constexpr int kTiles = F == Grouped::GateUp ? FR / 2 : FR;  // output tiles per wave
   int tid = threadIdx.x;
   // opaque per instantiation: the compiler otherwise hoists the address
   // arithmetic of every M-tile count above the branch between them and spills
@@ -184,10 +186,10 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
   const int rowq = K * P::kElemBytes / 16;
   const int ntiles = (F == Grouped::GateUp ? p.I : p.H) / 16;
   const int mt0 = MG == 1 ? 0 : (wave & 1) * MT;  // this wave's first M-tile
-  const int tile0 = (nblk * (4 / MG) + wave / MG) * kTiles;
+  const int tile0 = (run * (4 / MG) + wave / MG) * kTiles;
 
-  const uint4* w[kGrpFrags];
-  int wbytes[kGrpFrags];
+  const uint4* w[FR];
+  int wbytes[FR];
   int wstride;
   if (F == Grouped::GateUp) {
     const int npairs = (ntiles + 1) / 2, pair = tile0 / 2;
@@ -195,16 +197,18 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
     const uint4* base = uniform_ptr(static_cast<const uint4*>(p.w_gate_up) +
                                     (static_cast<size_t>(e) * npairs + (in ? pair : 0)) * KC * 4 * kWave);
     wstride = 4 * kWave;
-    // fragments gate 2p, gate 2p + 1, up 2p, up 2p + 1 of a chunk lie side by side
+    // fragments gate 2p, gate 2p + 1, up 2p, up 2p + 1 of a chunk lie side by
+    // side; one tile takes its gate and its up fragment
 #pragma unroll
-    for (int f = 0; f < kGrpFrags; ++f) {
-      w[f] = base + f * kWave;
-      wbytes[f] = in ? (KC * 4 - f) * kWave * 16 : 0;
+    for (int f = 0; f < FR; ++f) {
+      const int pos = FR == 4 ? f : 2 * f + (tile0 & 1);
+      w[f] = base + pos * kWave;
+      wbytes[f] = in ? (KC * 4 - pos) * kWave * 16 : 0;
     }
   } else {
     wstride = kWave;
 #pragma unroll
-    for (int f = 0; f < kGrpFrags; ++f) {
+    for (int f = 0; f < FR; ++f) {
       const bool in = tile0 + f < ntiles;
       w[f] = uniform_ptr(static_cast<const uint4*>(p.w_down) +
                          (static_cast<size_t>(e) * ntiles + (in ? tile0 + f : 0)) * KC * kWave);
@@ -226,12 +230,12 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
     gr.slot[tid] = slot;
     gr.gate[tid] = p.topk_gate[slot];
   }
-  floatx4 acc[kGrpFrags][MT];
+  floatx4 acc[FR][MT];
 #pragma unroll
-  for (int f = 0; f < kGrpFrags; ++f)
+  for (int f = 0; f < FR; ++f)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[f][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  grouped_product<P, MT, MG>(w, wbytes, wstride, xrow, KC, mt0, lds, acc);
+  grouped_product<P, MT, MG, FR>(w, wbytes, wstride, xrow, KC, mt0, lds, acc);
 
   // Lane (r, g) holds rows 4g .. 4g + 3 of column r of each tile.  Each M-tile
   // goes through this wave's part of the LDS, so the rows leave in 16-byte
@@ -240,7 +244,7 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
   constexpr int kOutEb = F == Grouped::GateUp ? P::kElemBytes : 4;
   constexpr int kRowPieces = kTiles * kOutEb;           // 16-byte pieces per row
   constexpr int kRowStride = kRowPieces * 16 + 16;      // bytes, padded
-  constexpr int kRowsPerStore = kWave / kRowPieces;
+  constexpr int kRowsPerStore = kWave / kRowPieces < 16 ? kWave / kRowPieces : 16;
   static_assert(16 * kRowStride * 4 <= kGrpLds<P> * 16, "one M-tile per wave fits");
   char* mine = reinterpret_cast<char*>(lds) + wave * 16 * kRowStride;
   const int nt = min(kTiles, ntiles - tile0);  // valid tiles of this wave (may be <= 0)
@@ -253,8 +257,8 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
       char* row = mine + (4 * g + i) * kRowStride + r * kOutEb;
       if (F == Grouped::GateUp) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const float v = silu_mul(acc[j][mt][i], acc[2 + j][mt][i]);
+        for (int j = 0; j < kTiles; ++j) {
+          const float v = silu_mul(acc[j][mt][i], acc[kTiles + j][mt][i]);
           if (P::kElemBytes == 2)
             *reinterpret_cast<uint16_t*>(row + 16 * j * kOutEb) = float_to_bf16_bits(v);
           else
@@ -263,7 +267,7 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
       } else {
         const float gate = gr.gate[min(m0 + 4 * g + i, rows - 1)];
 #pragma unroll
-        for (int f = 0; f < kGrpFrags; ++f) *reinterpret_cast<float*>(row + 16 * f * kOutEb) = gate * acc[f][mt][i];
+        for (int f = 0; f < FR; ++f) *reinterpret_cast<float*>(row + 16 * f * kOutEb) = gate * acc[f][mt][i];
       }
     }
     wave_lds_sync();
@@ -272,8 +276,8 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
     for (int q = 0; q < 16 / kRowsPerStore; ++q) {
       const int lr = q * kRowsPerStore + lane / kRowPieces;
       const int m = m0 + lr;
-      const uint4 v = *reinterpret_cast<const uint4*>(mine + lr * kRowStride + pc * 16);
-      if (m < rows && pc < nt * kOutEb) {
+      const uint4 v = *reinterpret_cast<const uint4*>(mine + min(lr, 15) * kRowStride + pc * 16);
+      if (lane < kRowsPerStore * kRowPieces && m < rows && pc < nt * kOutEb) {
         if (F == Grouped::GateUp)
           reinterpret_cast<uint4*>(static_cast<char*>(p.act) +
                                    (static_cast<size_t>(row0 + m) * p.I + tile0 * 16) * kOutEb)[pc] = v;
@@ -285,61 +289,101 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
   }
 }
 
+// One output run (or half run) of an item of up to kGrpTileM M-tiles.
+template <class P, Grouped F, int FR>
+__device__ __forceinline__ void grouped_small(const ForwardParams& p, int e, int row0, int rows, int run, uint4* lds,
+                                              GroupedRows<P>& gr) {
+  const int mt = (rows + 15) / 16;
+  if (mt == 1) grouped_item<P, F, 1, 1, FR>(p, e, row0, rows, run, lds, gr);
+  else if (kGrpTileM<P> == 2 || mt == 2) grouped_item<P, F, 2, 1, FR>(p, e, row0, rows, run, lds, gr);
+  else if constexpr (kGrpTileM<P> > 2) {
+    if (mt == 3) grouped_item<P, F, 3, 1, FR>(p, e, row0, rows, run, lds, gr);
+    else if (mt == 4) grouped_item<P, F, 4, 1, FR>(p, e, row0, rows, run, lds, gr);
+    else if (mt <= 6) grouped_item<P, F, 6, 1, FR>(p, e, row0, rows, run, lds, gr);
+    else grouped_item<P, F, 8, 1, FR>(p, e, row0, rows, run, lds, gr);
+  }
+}
+
 // Items come in groups of the workgroups that share one item's rows, group
 // after group round-robin over the XCDs (workgroup b runs on XCD b % 8), so
 // the rows are read from one XCD's L2.  An item of more than kGrpTileM M-tiles
-// runs two M groups over each half of its run in turn, so its weights still
-// come from HBM once; those loads use the default cache policy (the second M
-// group reads the same lines: 229 -> 215 us at 32 x 60 nodes), all others are
-// non-temporal (478 against 530 us on the wide layer).  Every item has the
-// same number of workgroups: workgroups that left at once held back the
-// dispatch of the other XCDs (428 of 512 resident).
+// runs two M groups over one weight stream, so its weights come from HBM once;
+// those loads use the default cache policy (the second M group reads the same
+// lines: 229 -> 215 us at 32 x 60 nodes), all others are non-temporal (478
+// against 530 us on the wide layer).
+//
+// A workgroup covers one of an item's `nblocks` runs, or half a run for the big
+// items, which come first, and for the last n_split items: shorter workgroups
+// at the end even out the finish.  With whole runs everywhere, on average 365
+// (4 x 60 nodes, H = 2048, I = 768) to 430 (8 x 64, H = 4096, I = 1536) of the
+// 512 resident workgroups were at work.  Steps, us, whole / half runs: 4 x 60
+// 210 / 199, 32 x 60 413 / 403, 7 x 60 with H = 256, I = 1664, top-4 89 / 75;
+// 8 x 64 (H = 4096) even.
 template <class P, Grouped F>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void grouped_kernel(ForwardParams p,
-                                                                                              int nblocks) {
+                                                                                              int nblocks,
+                                                                                              int n_split) {
   __shared__ uint4 lds[kGrpLds<P>];
   __shared__ GroupedRows<P> gr;
-  const int slot = blockIdx.x / 8;
-  const int item = (slot / nblocks) * 8 + blockIdx.x % 8, nblk = slot % nblocks;
-  if (item >= *p.n_items) return;
+  const int xcd = blockIdx.x % 8;
+  const int n_items = *p.n_items, n_big = *p.n_active;
+  const int n_whole = max(n_big, n_items - n_split);  // items [n_big, n_whole) take whole runs
+  auto on_xcd = [&](int n) { return (n + 7 - xcd) / 8; };  // of the first n items
+  const int big = on_xcd(n_big), whole = on_xcd(n_whole);
+  int slot = blockIdx.x / 8, item;
+  bool half = true;
+  if (slot < 2 * nblocks * big) {
+    item = slot / (2 * nblocks);
+    slot -= item * 2 * nblocks;
+  } else if (slot -= 2 * nblocks * big; slot < nblocks * (whole - big)) {
+    half = false;
+    item = slot / nblocks;
+    slot -= item * nblocks;
+    item += big;
+  } else {
+    slot -= nblocks * (whole - big);
+    item = slot / (2 * nblocks);
+    slot -= item * 2 * nblocks;
+    item += whole;
+  }
+  item = item * 8 + xcd;
+  if (item >= n_items) return;
   const int4 d = p.items[item];
   const int e = __builtin_amdgcn_readfirstlane(d.x);
   const int row0 = __builtin_amdgcn_readfirstlane(d.y);
   const int rows = __builtin_amdgcn_readfirstlane(d.z);
-  const int mt = (rows + 15) / 16;
-  if (mt <= kGrpTileM<P>) {
-    if (mt == 1) grouped_item<P, F, 1, 1>(p, e, row0, rows, nblk, lds, gr);
-    else if (kGrpTileM<P> == 2 || mt == 2) grouped_item<P, F, 2, 1>(p, e, row0, rows, nblk, lds, gr);
-    else if constexpr (kGrpTileM<P> > 2) {
-      if (mt == 3) grouped_item<P, F, 3, 1>(p, e, row0, rows, nblk, lds, gr);
-      else if (mt == 4) grouped_item<P, F, 4, 1>(p, e, row0, rows, nblk, lds, gr);
-      else if (mt <= 6) grouped_item<P, F, 6, 1>(p, e, row0, rows, nblk, lds, gr);
-      else grouped_item<P, F, 8, 1>(p, e, row0, rows, nblk, lds, gr);
-    }
+  if (item >= n_big) {
+    if (half) grouped_small<P, F, 2>(p, e, row0, rows, slot, lds, gr);
+    else grouped_small<P, F, 4>(p, e, row0, rows, slot, lds, gr);
+  } else if constexpr (kGrpTileM<P> > 2) {
+    if (rows <= 160) grouped_item<P, F, 5, 2, 4>(p, e, row0, rows, slot, lds, gr);
+    else grouped_item<P, F, 6, 2, 4>(p, e, row0, rows, slot, lds, gr);
   } else {
-    for (int h = 0; h < 2; ++h) {  // the two halves of the run
-      if constexpr (kGrpTileM<P> > 2) {
-        if (mt <= 10) grouped_item<P, F, 5, 2>(p, e, row0, rows, 2 * nblk + h, lds, gr);
-        else grouped_item<P, F, 6, 2>(p, e, row0, rows, 2 * nblk + h, lds, gr);
-      } else {
-        grouped_item<P, F, 2, 2>(p, e, row0, rows, 2 * nblk + h, lds, gr);
-      }
-      __syncthreads();  // the LDS parts of the waves are staging space again
-    }
+    grouped_item<P, F, 2, 2, 4>(p, e, row0, rows, slot, lds, gr);
   }
+}
+
+// Half runs for the last items: as many as make one round of the resident
+// workgroups, two per CU (half as many measured 1-3 % slower at 4 x 60 nodes,
+// twice as many 2-4 % at 4 x 60 and 32 x 60: a half run stages the item's rows
+// again).  Experts sorted by rows as well: 4 x 60 3 % faster, but 8 x 64
+// (H = 4096) up to 2 % slower.
+template <class P, Grouped F>
+hipError_t launch_grouped_pass(const ForwardParams& p, int max_items, int nblocks, hipStream_t stream) {
+  constexpr int kHalfRuns = 512;
+  const int n_split = (kHalfRuns / 2 + nblocks - 1) / nblocks;
+  const int max_big = static_cast<int>(static_cast<long long>(p.T) * p.k / (p.big_rows + 1));
+  const long long groups = (max_items + 7) / 8 + (max_big + 7) / 8 + (std::min(n_split, max_items) + 7) / 8;
+  // far beyond what the slot rows of one device's memory allow
+  if (8 * groups * nblocks > 0x7fffffffll) return hipErrorInvalidValue;
+  grouped_kernel<P, F><<<static_cast<unsigned>(8 * groups * nblocks), 256, 0, stream>>>(p, nblocks, n_split);
+  return hipGetLastError();
 }
 
 template <class P>
 hipError_t launch_grouped_path(const ForwardParams& p, int max_items, hipStream_t stream) {
-  const int groups = (max_items + 7) / 8 * 8;
-  const int gu = (p.I / 16 + 7) / 8, dn = (p.H / 16 + 15) / 16;
-  // far beyond what the slot rows of one device's memory allow
-  if (static_cast<long long>(groups) * (gu > dn ? gu : dn) > 0x7fffffffll) return hipErrorInvalidValue;
-  grouped_kernel<P, Grouped::GateUp><<<groups * gu, 256, 0, stream>>>(p, gu);
-  const hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  grouped_kernel<P, Grouped::Down><<<groups * dn, 256, 0, stream>>>(p, dn);
-  return hipGetLastError();
+  const hipError_t err = launch_grouped_pass<P, Grouped::GateUp>(p, max_items, (p.I / 16 + 7) / 8, stream);
+  return err != hipSuccess ? err : launch_grouped_pass<P, Grouped::Down>(p, max_items, (p.H / 16 + 15) / 16, stream);
 }
 
 }  // namespace

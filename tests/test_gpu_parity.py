@@ -477,8 +477,6 @@ def test_forward_parity_m_groups(gpu, dtype):
     check_forward(got, ref, cfg.dtype, f"M groups {dtype}")
 
 
-# one GPU's share of a tensor-parallel split over I: thin I gives the column-tile
-# down pass 3-step stages (one column tile at H = 1024, two at H = 4096)
 # routing rows of 16 and 17 slots (the kernels hold rows of up to 8, 16 or 32)
 # on both FFN paths; one token alone takes workgroups without an item
 @pytest.mark.parametrize("T,k", [(1, 16), (20, 16), (20, 17), (300, 16), (300, 17)])
@@ -517,6 +515,27 @@ def test_forward_parity_grouped_edges(gpu, dtype, T, counts):
     check_forward(got, ref, cfg.dtype, f"grouped edges T={T} {dtype}")
 
 
+# the three kinds of items of the grouped GEMMs in one block: one expert above
+# 128 rows (half runs, two M groups), whole runs, and the last items' half runs;
+# 18 tiles of I and 34 of H end inside a run and inside a half run
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("H,I", [(544, 288), (288, 96)])
+def test_forward_parity_grouped_runs(gpu, dtype, H, I):
+    T, E, k = 300, 128, 4
+    cfg = W.LayerConfig("runs", 970 + H, dtype, T=T, B=1, H=H, E=E, k=k, I=I, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    rng = np.random.default_rng(H)
+    h32 = rng.standard_normal((T, H)).astype(np.float32)
+    gate = rng.random((T, k)).astype(np.float32)
+    idx = (1 + (k * np.arange(T)[:, None] + np.arange(k)) % (E - 1)).astype(np.int32)
+    idx[rng.permutation(T)[:150], 1] = 0
+    got, h64, (wg, wu, wd) = forward_case(cfg, idx, gate, h32)
+    ref = O.moe_forward_grouped(h64, wg, wu, wd, idx, gate, cfg.dtype)
+    check_forward(got, ref, cfg.dtype, f"grouped runs H={H} I={I} {dtype}")
+
+
+# one GPU's share of a tensor-parallel split over I: thin I gives the column-tile
+# down pass 3-step stages (one column tile at H = 1024, two at H = 4096)
 @pytest.mark.parametrize("H,I,T,E", [(1024, 96, 32, 64), (4096, 192, 64, 32)])
 def test_forward_parity_thin_shard(gpu, H, I, T, E):
     cfg = W.LayerConfig("thin", 96 + I, "bf16", T=T, B=1, H=H, E=E, k=8, I=I, depth_max=6,
