@@ -148,61 +148,74 @@ __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, cons
 // ---------------------------------------------------------------------------
 // dispatch of the grouped path: CSR of (expert -> slot ids in node order) and
 // the items of the grouped GEMMs.  One workgroup per kDispatchChunk nodes.
-// Every workgroup counts all routing rows (LDS atomics; at 1920 nodes x 8
-// slots that is 15 per thread) into the block's totals and into the counts of
-// the nodes before its own, so no workgroup waits for another; positions
-// inside an expert's list then come from per-expert bitmasks of its own
-// nodes, so the order is deterministic (node order).  Workgroup 0 writes the
-// items: an expert's rows in equal runs of whole M-tiles, at most
-// p.item_rows each.
+// Every workgroup counts all routing rows, so no workgroup waits for another:
+// its own nodes go into per-expert bitmasks, which give both their count and
+// their positions (in node order, so the result is deterministic), the nodes
+// before and after into counters.  That is one LDS atomic per slot; a wave's
+// atomics on a popular expert run one after the other and bound the kernel.
+// A wave beyond those that write the lists writes the items (workgroup 0): an
+// expert's rows in equal runs of whole M-tiles, at most p.item_rows each.
 // ---------------------------------------------------------------------------
 template <int KMAX>
 __global__ __launch_bounds__(kDispatchThreads) void dispatch_kernel(ForwardParams p) {
   constexpr int words = kDispatchChunk / 32;
+  constexpr int kItemWave = kDispatchChunk / kWave;  // the first wave without a node of its own
   __shared__ int s_cnt[kMaxExperts];
   __shared__ int s_before[kMaxExperts];
   __shared__ int s_off[kMaxExperts + 1];
   __shared__ int s_active[kMaxExperts];
   __shared__ uint32_t s_mask[kMaxExperts * words];
+  __shared__ int s_nact;
   const int tid = threadIdx.x;
   const int E = p.E, k = p.k, T = p.T;
   const int c0 = blockIdx.x * kDispatchChunk;  // first node of this workgroup
+  // the node whose list entries this thread writes, loaded beside the clearing
+  int own[KMAX];
+  uint32_t own_valid = 0u;
+  const int t_own = c0 + tid;
+  if (tid < kDispatchChunk && t_own < T)
+    own_valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t_own) * k, k, E, own);
   for (int e = tid; e < E; e += kDispatchThreads) s_cnt[e] = s_before[e] = 0;
   for (int i = tid; i < E * words; i += kDispatchThreads) s_mask[i] = 0u;
   __syncthreads();
-  int ev[KMAX];
-  for (int t = tid; t < T; t += kDispatchThreads) {
-    const uint32_t valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t) * k, k, E, ev);
-    const int tl = t - c0;
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-      if (valid & (1u << j)) {
-        atomicAdd(&s_cnt[ev[j]], 1);
-        if (tl < 0) atomicAdd(&s_before[ev[j]], 1);
-        else if (tl < kDispatchChunk) atomicOr(&s_mask[ev[j] * words + (tl >> 5)], 1u << (tl & 31));
-      }
-    }
+  for (int j = 0; j < KMAX; ++j)
+    if (own_valid & (1u << j)) atomicOr(&s_mask[own[j] * words + (tid >> 5)], 1u << (tid & 31));
+  // the other nodes: i counts the T nodes without the workgroup's own
+  const int n_own = min(kDispatchChunk, T - c0);
+  for (int i = tid; i < T - n_own; i += kDispatchThreads) {
+    const int t = i < c0 ? i : i + n_own;
+    int* cnt = i < c0 ? s_before : s_cnt;
+    int ev[KMAX];
+    const uint32_t valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t) * k, k, E, ev);
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j)
+      if (valid & (1u << j)) atomicAdd(&cnt[ev[j]], 1);
+  }
+  __syncthreads();
+  for (int e = tid; e < E; e += kDispatchThreads) {
+    int c = s_cnt[e] + s_before[e];
+#pragma unroll
+    for (int w = 0; w < words; ++w) c += __popc(s_mask[e * words + w]);
+    s_cnt[e] = c;
   }
   __syncthreads();
   if (tid < kWave) {
     const int na = scan_experts(s_cnt, s_off, s_active, nullptr, E, tid);
-    if (blockIdx.x == 0) write_grouped_items(p, s_cnt, s_off, s_active, na, tid);
+    if (tid == 0) s_nact = na;
   }
   __syncthreads();
-  const int t = c0 + tid;
-  if (tid < kDispatchChunk && t < T) {
-    const uint32_t valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t) * k, k, E, ev);
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-      if (valid & (1u << j)) {
-        const uint32_t* m = s_mask + ev[j] * words;
-        int pos = s_off[ev[j]] + s_before[ev[j]] + __popc(m[tid >> 5] & ((1u << (tid & 31)) - 1u));
+  for (int j = 0; j < KMAX; ++j) {
+    if (own_valid & (1u << j)) {
+      const uint32_t* m = s_mask + own[j] * words;
+      int pos = s_off[own[j]] + s_before[own[j]] + __popc(m[tid >> 5] & ((1u << (tid & 31)) - 1u));
 #pragma unroll
-        for (int w = 0; w < words; ++w) pos += w < (tid >> 5) ? __popc(m[w]) : 0;
-        p.ent_slot[pos] = t * k + j;
-      }
+      for (int w = 0; w < words; ++w) pos += w < (tid >> 5) ? __popc(m[w]) : 0;
+      p.ent_slot[pos] = t_own * k + j;
     }
   }
+  if (blockIdx.x == 0 && wave_id() == kItemWave) write_grouped_items(p, s_cnt, s_off, s_active, s_nact, lane_id());
 }
 
 // ---------------------------------------------------------------------------
