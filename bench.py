@@ -96,7 +96,8 @@ def parse():
 # sources still hash to H.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "moe_forward_traffic.md")
 FFN_SOURCES = ["paper_2608_02989_amd/csrc/forward.hip", "paper_2608_02989_amd/csrc/grouped.hip",
-               "paper_2608_02989_amd/csrc/ffn_common.hpp", "paper_2608_02989_amd/csrc/common.hpp"]
+               "paper_2608_02989_amd/csrc/grouped_plan.hpp", "paper_2608_02989_amd/csrc/ffn_common.hpp",
+               "paper_2608_02989_amd/csrc/common.hpp"]
 
 
 def ffn_source_hash() -> str:

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "ffn_common.hpp"
+#include "grouped_plan.hpp"
 
 namespace amoe {
 
@@ -131,13 +132,11 @@ __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, cons
       const int a = a0 + tid;
       const int e = a < na ? active[a] : 0;
       const int c = a < na ? cnt[e] : 0;
-      const int tiles = (c + 15) / 16;
-      const int nb = (c + p.item_rows - 1) / p.item_rows;
-      const int per = nb > 0 ? 16 * ((tiles + nb - 1) / nb) : 16;
-      const int nr = (min(per, c) > p.big_rows) == (big != 0) ? (c + per - 1) / per : 0;  // <= nb
-      const int incl = wave_incl_scan_i32(nr);
-      for (int m = 0; m < nr; ++m)
-        p.items[base + incl - nr + m] = make_int4(e, off[e] + per * m, min(per, c - per * m), 0);
+      const ItemSplit sp = split_rows(c, p.item_rows, p.big_rows);
+      const int n = sp.big == (big != 0) ? sp.items : 0;
+      const int incl = wave_incl_scan_i32(n);
+      for (int m = 0; m < n; ++m)
+        p.items[base + incl - n + m] = make_int4(e, off[e] + sp.rows * m, min(sp.rows, c - sp.rows * m), 0);
       base += lane_value(incl, kWave - 1);
     }
     if (big != 0 && tid == 0) *p.n_active = base;
@@ -998,10 +997,8 @@ hipError_t launch_pack(const void* src, int is_bf16, int E, int N, int K, void* 
   return hipGetLastError();
 }
 
-// most items of the grouped path: one per active expert and one more per full item
-int grouped_max_items(int T, int E, int k, int is_bf16) {
-  const int slots = T * k;
-  return (E < slots ? E : slots) + slots / grouped_item_rows(is_bf16);
+int max_grouped_items(int T, int E, int k, int is_bf16) {
+  return grouped_max_items(T * k, E, grouped_item_rows(is_bf16 ? 2 : 4));
 }
 
 // workspace: [cnt E | off E+1 | active E | n_active | n_items] ints, CSR slot
@@ -1016,7 +1013,7 @@ size_t forward_workspace_bytes(int T, int H, int I, int E, int k, int is_bf16) {
     const size_t items = (slots + 15) / 16 + (static_cast<size_t>(E) < slots ? E : slots);
     return head + align256(items * sizeof(int4));
   }
-  return head + align256(static_cast<size_t>(grouped_max_items(T, E, k, is_bf16)) * sizeof(int4)) +
+  return head + align256(static_cast<size_t>(max_grouped_items(T, E, k, is_bf16)) * sizeof(int4)) +
          align256(slots * H * sizeof(float));
 }
 
@@ -1040,7 +1037,7 @@ void forward_carve(void* ws, ForwardParams& p) {
     p.ys = nullptr;
   } else {
     p.items = reinterpret_cast<int4*>(c);
-    c += align256(static_cast<size_t>(grouped_max_items(p.T, p.E, p.k, p.is_bf16)) * sizeof(int4));
+    c += align256(static_cast<size_t>(max_grouped_items(p.T, p.E, p.k, p.is_bf16)) * sizeof(int4));
     p.ys = reinterpret_cast<float*>(c);
   }
 }
@@ -1061,8 +1058,8 @@ hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
     if (err != hipSuccess) return err;
     return p.is_bf16 ? launch_down_col<Bf16Path>(p, cs, stream) : launch_down_col<F32Path>(p, cs, stream);
   }
-  p.item_rows = grouped_item_rows(p.is_bf16);
-  p.big_rows = grouped_big_rows(p.is_bf16);
+  p.item_rows = grouped_item_rows(p.is_bf16 ? 2 : 4);
+  p.big_rows = grouped_big_rows(p.is_bf16 ? 2 : 4);
   const int chunks = (p.T + kDispatchChunk - 1) / kDispatchChunk;
   if (p.k <= 8)
     dispatch_kernel<8><<<chunks, kDispatchThreads, 0, stream>>>(p);
@@ -1072,7 +1069,7 @@ hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
     dispatch_kernel<kMaxTopK><<<chunks, kDispatchThreads, 0, stream>>>(p);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  err = launch_grouped(p, grouped_max_items(p.T, p.E, p.k, p.is_bf16), stream);
+  err = launch_grouped(p, max_grouped_items(p.T, p.E, p.k, p.is_bf16), stream);
   if (err != hipSuccess) return err;
   const int hblocks = (p.H / 4 + 255) / 256;
   const dim3 cgrid(static_cast<unsigned>(hblocks) * static_cast<unsigned>(p.T));

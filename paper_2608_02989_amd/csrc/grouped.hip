@@ -20,10 +20,10 @@
 // per wave at three workgroups per CU (482 / 240 us gate/up), four weight
 // stages in flight (484 / 223), K split two ways (486 / 245) or four ways
 // (533 / 376), two M groups for every item (615 / 248).
-#include <algorithm>
 #include <type_traits>
 
 #include "ffn_common.hpp"
+#include "grouped_plan.hpp"
 
 namespace amoe {
 
@@ -39,11 +39,11 @@ enum class Grouped { GateUp, Down };
 // thread also holds twice the rows in flight: 6.  The fp32 path keeps a second
 // accumulator set (below): 3.
 template <class P>
-constexpr int kGrpTileM = P::kElemBytes == 2 ? 8 : 2;
+constexpr int kGrpTileM = grouped_tile_m(P::kElemBytes);
 template <class P>
-constexpr int kGrpTileM2 = P::kElemBytes == 2 ? 6 : 2;
+constexpr int kGrpTileM2 = grouped_tile_m2(P::kElemBytes);
 template <class P>
-constexpr int kGrpMaxRows = 2 * 16 * kGrpTileM2<P>;  // rows of an item
+constexpr int kGrpMaxRows = grouped_item_rows(P::kElemBytes);
 
 // Adds the products of `rows` rows of one item into acc and returns with the
 // workgroup's LDS free.  w[f] / wbytes[f]: run of weight fragment f (a run of
@@ -321,62 +321,36 @@ __device__ __forceinline__ void grouped_small(const ForwardParams& p, int e, int
 // 8 x 64 (H = 4096) even.
 template <class P, Grouped F>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void grouped_kernel(ForwardParams p,
-                                                                                              int nblocks,
-                                                                                              int n_split) {
+                                                                                              int nblocks) {
   __shared__ uint4 lds[kGrpLds<P>];
   __shared__ GroupedRows<P> gr;
-  const int xcd = blockIdx.x % 8;
   const int n_items = *p.n_items, n_big = *p.n_active;
-  const int n_whole = max(n_big, n_items - n_split);  // items [n_big, n_whole) take whole runs
-  auto on_xcd = [&](int n) { return (n + 7 - xcd) / 8; };  // of the first n items
-  const int big = on_xcd(n_big), whole = on_xcd(n_whole);
-  int slot = blockIdx.x / 8, item;
-  bool half = true;
-  if (slot < 2 * nblocks * big) {
-    item = slot / (2 * nblocks);
-    slot -= item * 2 * nblocks;
-  } else if (slot -= 2 * nblocks * big; slot < nblocks * (whole - big)) {
-    half = false;
-    item = slot / nblocks;
-    slot -= item * nblocks;
-    item += big;
-  } else {
-    slot -= nblocks * (whole - big);
-    item = slot / (2 * nblocks);
-    slot -= item * 2 * nblocks;
-    item += whole;
-  }
-  item = item * 8 + xcd;
-  if (item >= n_items) return;
-  const int4 d = p.items[item];
+  const GroupedShare sh = grouped_share(blockIdx.x, n_items, n_big, nblocks);
+  if (sh.item >= n_items) return;
+  const int4 d = p.items[sh.item];
+  const int run = __builtin_amdgcn_readfirstlane(sh.run);  // without this the gate/up kernel spills 65 registers, not 6
   const int e = __builtin_amdgcn_readfirstlane(d.x);
   const int row0 = __builtin_amdgcn_readfirstlane(d.y);
   const int rows = __builtin_amdgcn_readfirstlane(d.z);
-  if (item >= n_big) {
-    if (half) grouped_small<P, F, 2>(p, e, row0, rows, slot, lds, gr);
-    else grouped_small<P, F, 4>(p, e, row0, rows, slot, lds, gr);
+  if (sh.item >= n_big) {
+    if (sh.half) grouped_small<P, F, 2>(p, e, row0, rows, run, lds, gr);
+    else grouped_small<P, F, 4>(p, e, row0, rows, run, lds, gr);
   } else if constexpr (kGrpTileM<P> > 2) {
-    if (rows <= 160) grouped_item<P, F, 5, 2, 4>(p, e, row0, rows, slot, lds, gr);
-    else grouped_item<P, F, 6, 2, 4>(p, e, row0, rows, slot, lds, gr);
+    if (rows <= 160) grouped_item<P, F, 5, 2, 4>(p, e, row0, rows, run, lds, gr);
+    else grouped_item<P, F, 6, 2, 4>(p, e, row0, rows, run, lds, gr);
   } else {
-    grouped_item<P, F, 2, 2, 4>(p, e, row0, rows, slot, lds, gr);
+    grouped_item<P, F, 2, 2, 4>(p, e, row0, rows, run, lds, gr);
   }
 }
 
-// Half runs for the last items: as many as make one round of the resident
-// workgroups, two per CU (half as many measured 1-3 % slower at 4 x 60 nodes,
-// twice as many 2-4 % at 4 x 60 and 32 x 60: a half run stages the item's rows
-// again).  Experts sorted by rows as well: 4 x 60 3 % faster, but 8 x 64
-// (H = 4096) up to 2 % slower.
+// Items sorted by rows as well measured 3 % faster at 4 x 60 nodes, but up to 2 %
+// slower at 8 x 64 (H = 4096).
 template <class P, Grouped F>
 hipError_t launch_grouped_pass(const ForwardParams& p, int max_items, int nblocks, hipStream_t stream) {
-  constexpr int kHalfRuns = 512;
-  const int n_split = (kHalfRuns / 2 + nblocks - 1) / nblocks;
-  const int max_big = static_cast<int>(static_cast<long long>(p.T) * p.k / (p.big_rows + 1));
-  const long long groups = (max_items + 7) / 8 + (max_big + 7) / 8 + (std::min(n_split, max_items) + 7) / 8;
+  const long long grid = grouped_workgroups(p.T * p.k, max_items, p.big_rows, nblocks);
   // far beyond what the slot rows of one device's memory allow
-  if (8 * groups * nblocks > 0x7fffffffll) return hipErrorInvalidValue;
-  grouped_kernel<P, F><<<static_cast<unsigned>(8 * groups * nblocks), 256, 0, stream>>>(p, nblocks, n_split);
+  if (grid > 0x7fffffffll) return hipErrorInvalidValue;
+  grouped_kernel<P, F><<<static_cast<unsigned>(grid), 256, 0, stream>>>(p, nblocks);
   return hipGetLastError();
 }
 
@@ -387,10 +361,6 @@ hipError_t launch_grouped_path(const ForwardParams& p, int max_items, hipStream_
 }
 
 }  // namespace
-
-int grouped_item_rows(int is_bf16) { return is_bf16 ? kGrpMaxRows<Bf16Path> : kGrpMaxRows<F32Path>; }
-
-int grouped_big_rows(int is_bf16) { return 16 * (is_bf16 ? kGrpTileM<Bf16Path> : kGrpTileM<F32Path>); }
 
 hipError_t launch_grouped(const ForwardParams& p, int max_items, hipStream_t stream) {
   return p.is_bf16 ? launch_grouped_path<Bf16Path>(p, max_items, stream)

@@ -1,0 +1,89 @@
+// How the grouped GEMMs split an expert's dispatched rows into items and the
+// items over workgroups.  Plain constexpr arithmetic, used by the dispatch, the
+// kernels and the host code that sizes their grids.
+#pragma once
+
+namespace amoe {
+
+// M-tiles per wave, in one M group and in each of two (see grouped.hip)
+constexpr int grouped_tile_m(int elem_bytes) { return elem_bytes == 2 ? 8 : 2; }
+constexpr int grouped_tile_m2(int elem_bytes) { return elem_bytes == 2 ? 6 : 2; }
+// most rows of an item; items above grouped_big_rows take two M groups and half runs
+constexpr int grouped_item_rows(int elem_bytes) { return 2 * 16 * grouped_tile_m2(elem_bytes); }
+constexpr int grouped_big_rows(int elem_bytes) { return 16 * grouped_tile_m(elem_bytes); }
+
+// An expert's `count` rows in equal runs of whole M-tiles, at most item_rows
+// each: items m = 0 .. items - 1 of min(rows, count - rows m) rows.  All of them
+// are big or none, whatever the last one holds.
+struct ItemSplit {
+  int rows, items;
+  bool big;
+};
+constexpr ItemSplit split_rows(int count, int item_rows, int big_rows) {
+  const int tiles = (count + 15) / 16;
+  const int most = (count + item_rows - 1) / item_rows;
+  const int rows = most > 0 ? 16 * ((tiles + most - 1) / most) : 16;
+  return {rows, (count + rows - 1) / rows, (rows < count ? rows : count) > big_rows};
+}
+
+// most items of a block of `slots` routing entries: one per active expert and
+// one more per full item
+constexpr int grouped_max_items(int slots, int E, int item_rows) {
+  return (E < slots ? E : slots) + slots / item_rows;
+}
+
+// The last items take half runs, as many of them as make one round of the
+// resident workgroups, two per CU (half as many measured 1-3 % slower at 4 x 60
+// nodes, twice as many 2-4 % at 4 x 60 and 32 x 60: a half run stages the item's
+// rows again).
+constexpr int grouped_split_items(int nblocks) {
+  constexpr int kHalfRuns = 512;
+  return (kHalfRuns / 2 + nblocks - 1) / nblocks;
+}
+
+// Workgroup `block`'s share: output run (or half run) `run` of an item; nothing
+// if item >= n_items.  The n_big big items come first and take half runs, as do
+// the last ones.  The items go round-robin over the XCDs (workgroup b
+// runs on XCD b % 8), all runs of one on the same XCD.
+struct GroupedShare {
+  int item, run;
+  bool half;
+};
+constexpr GroupedShare grouped_share(int block, int n_items, int n_big, int nblocks) {
+  const int n_split = grouped_split_items(nblocks);
+  const int xcd = block % 8;
+  const int n_whole = n_big > n_items - n_split ? n_big : n_items - n_split;  // items [n_big, n_whole) take whole runs
+  const int big = (n_big + 7 - xcd) / 8, whole = (n_whole + 7 - xcd) / 8;      // of the first n items on this XCD
+  int slot = block / 8, item = 0;
+  bool half = true;
+  if (slot < 2 * nblocks * big) {
+    item = slot / (2 * nblocks);
+    slot -= item * 2 * nblocks;
+  } else if (slot -= 2 * nblocks * big; slot < nblocks * (whole - big)) {
+    half = false;
+    item = slot / nblocks;
+    slot -= item * nblocks;
+    item += big;
+  } else {
+    slot -= nblocks * (whole - big);
+    item = slot / (2 * nblocks);
+    slot -= item * 2 * nblocks;
+    item += whole;
+  }
+  return {item * 8 + xcd, slot, half};
+}
+
+// Workgroups that cover every item's nblocks runs for any routing of `slots`
+// entries: per XCD one whole run's workgroups for each item and as many again
+// for the big items and for the last ones.  There are at most slots / big_rows
+// big items: runs of big_rows / 16 + 1 M-tiles or more in each of n items make
+// more than n big_rows / 16 M-tiles, so the expert has at least n big_rows rows
+// although its last item may hold fewer (257 rows: 144 + 113).
+constexpr long long grouped_workgroups(int slots, int max_items, int big_rows, int nblocks) {
+  const int n_split = grouped_split_items(nblocks);
+  const int max_big = slots / big_rows;
+  const long long groups = (max_items + 7) / 8 + (max_big + 7) / 8 + ((n_split < max_items ? n_split : max_items) + 7) / 8;
+  return 8 * groups * nblocks;
+}
+
+}  // namespace amoe

@@ -91,9 +91,7 @@ struct ForwardParams {
   int big_rows;       // items of the grouped GEMMs above this size take two M groups and half runs
 };
 
-// grouped GEMMs of larger blocks (grouped.hip): rows per item, rows per M group, and both passes
-int grouped_item_rows(int is_bf16);
-int grouped_big_rows(int is_bf16);
+// grouped GEMMs of larger blocks (grouped.hip), both passes
 hipError_t launch_grouped(const ForwardParams& p, int max_items, hipStream_t stream);
 
 size_t forward_workspace_bytes(int T, int H, int I, int E, int k, int is_bf16);

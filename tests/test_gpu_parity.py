@@ -534,6 +534,33 @@ def test_forward_parity_grouped_runs(gpu, dtype, H, I):
     check_forward(got, ref, cfg.dtype, f"grouped runs H={H} I={I} {dtype}")
 
 
+# the most items of two M groups that a block's routing entries allow (experts
+# whose rows split into short big items: 65 = 48 + 17, 257 = 144 + 113): every
+# output run has a workgroup.  The workspace starts as NaN, so a run that nobody
+# computes shows.
+@pytest.mark.parametrize("dtype,T,k,groups", [("f32", 400, 8, [(49, 65), (15, 1)]),
+                                              ("bf16", 755, 7, [(20, 257), (1, 129), (16, 1)])])
+def test_forward_parity_most_big_items(gpu, dtype, T, k, groups):
+    counts = [c for n, c in groups for _ in range(n)]
+    E = len(counts)
+    cfg = W.LayerConfig("bigitems", 980 + T, dtype, T=T, B=1, H=4096, E=E, k=k, I=64, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    flat = np.full(T * k, -1, np.int32)
+    flat[:sum(counts)] = np.repeat(np.arange(E), counts)
+    idx = np.ascontiguousarray(flat.reshape(k, T).T)  # an expert's rows follow each other, so no token repeats one
+    rng = np.random.default_rng(T)
+    h32 = rng.standard_normal((T, cfg.H)).astype(np.float32)
+    gate = rng.random((T, k)).astype(np.float32)
+    hdev, h64 = hidden_for(cfg, h32)
+    wg, wu, wd = W.expert_weights_torch(cfg, 0, DEV)
+    ws = ops.forward_workspace(T, cfg.H, cfg.I, E, k, wg.dtype, DEV).fill_(0xFF)
+    say(f"forward most big items {dtype}")
+    y = ops.moe_forward(to_dev_hidden(cfg, hdev), ops.pack_gate_up_weights(wg, wu), ops.pack_expert_weights(wd),
+                        i32(idx), f32(gate), workspace=ws)
+    ref = O.moe_forward_grouped(h64, HostExperts(wg), HostExperts(wu), HostExperts(wd), idx, gate, cfg.dtype)
+    check_forward(y.cpu().numpy(), ref, cfg.dtype, f"most big items {dtype}")
+
+
 # one GPU's share of a tensor-parallel split over I: thin I gives the column-tile
 # down pass 3-step stages (one column tile at H = 1024, two at H = 4096)
 @pytest.mark.parametrize("H,I,T,E", [(1024, 96, 32, 64), (4096, 192, 64, 32)])
