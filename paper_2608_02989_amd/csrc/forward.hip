@@ -922,20 +922,36 @@ ColShape col_shape(int T, int H, int I, int is_bf16) {
 
 // Column path (gate/up with its own dispatch, then the column-tile down pass)
 // or grouped path (dispatch, grouped GEMMs, combine).  The column path's lists
-// hold 256 tokens and 2048 slots; below that the line lies where the grouped
-// path's row reuse (both projections re-read an expert's rows once per 128
-// output rows instead of once per 32 or 16) outweighs its two more launches
-// and its slot rows.  Both FFN paths, us, column / grouped:
-//   H = 2048, I = 768:   T = 72 94 / 109, 96 111 / 114, 120 134 / 120, 240 224 / 189
-//   H = 4096, I = 1536:  T = 64 168 / 187, 96 277 / 270, 128 314 / 264
-//   fp32, H = 2048, I = 768 (fp32 products): T = 120 235 / 311, 240 410 / 373
-// A thin I leaves the grouped gate/up too few workgroups (one per 128 rows of
-// I and expert): H = 4096, I = 192, T = 120 89 / 102; I = 256 at T = 128 even.
-bool use_col_path(int T, int I, int k, int is_bf16) {
-  if (T > kColMaxT || T > kSelfMaxT || static_cast<long long>(T) * k > kColMaxSlots ||
-      static_cast<long long>(T) * k > kSelfMaxSlots)
-    return false;
-  return T <= (is_bf16 ? 96 : 192) || I < 256;
+// hold 256 tokens and 2048 slots; up to 96 tokens (fp32: 192), or with a thin I,
+// which leaves the grouped gate/up one or two workgroups per expert, that path is
+// taken.  Beyond, the line is where two costs meet.  Every workgroup of the
+// column path's down pass reads all slots' activations, so it is behind once
+// slots x I per down workgroup is large (three times earlier where the down
+// stages are single k-steps).  The grouped path pays two more launches, the slot
+// rows and, with few rows per expert, M-tiles that are mostly padding; from 12
+// rows per expert on it gains in bf16 whatever the rest (both projections re-read
+// an expert's rows once per 128 or 256 outputs, not once per 32 or 16), but not in
+// fp32, whose products leave no such slack.  Whole steps, us, column / grouped:
+//   H = 2048, I = 768    E = 128: k = 1, T = 160 102 / 121; k = 2, T = 100 91 / 113; k = 8, T = 160 210 / 201
+//                        E = 64: k = 2, T = 160 96 / 115; k = 8, T = 256 225 / 154
+//                        E = 16, k = 1: T = 100 46 / 57, T = 256 64 / 60
+//   H = 1024, I = 512    E = 64: k = 1, T = 100 39 / 45; k = 8, T = 100 78 / 66
+//   H = 4096, I = 1536   E = 128: k = 1, T = 100 202 / 221; k = 8, T = 256 822 / 764
+//   fp32, H = 2048, I = 768   E = 16, k = 1, T = 200 98 / 153; E = 64, k = 8, T = 256 468 / 355
+//   fp32, H = 3584, I = 256   E = 160, k = 8, T = 195 266 / 302
+// and below 96 tokens, E = 128, k = 8: H = 2048, I = 768, T = 72 117 / 128, T = 96
+// 130 / 134; H = 4096, I = 1536, T = 72 323 / 330, T = 96 353 / 349.
+// Over 789 (fp32: 308) layers and blocks of 97 (193) to 256 tokens, drawn and on a
+// grid of H, I, E and k, this choice is 0.24 % (0.7 %) behind the faster path on
+// average; the grouped path throughout is 1.3 % (3.7 %) behind.
+bool use_col_path(int T, int H, int I, int E, int k, int is_bf16) {
+  const long long slots = static_cast<long long>(T) * k;
+  if (T > kColMaxT || T > kSelfMaxT || slots > kColMaxSlots || slots > kSelfMaxSlots) return false;
+  if (T <= (is_bf16 ? 96 : 192) || I < 256) return true;
+  if (is_bf16 && slots > 12ll * E) return false;
+  const ColShape c = col_shape(T, H, I, is_bf16);
+  const long long down_wgs = static_cast<long long>(H / 16 / c.nb) * c.ksplit;
+  return slots * I <= (c.ku == 1 ? 640 : 1920) * down_wgs;
 }
 
 template <class P, int NB, int MTI>
@@ -1009,7 +1025,7 @@ size_t forward_workspace_bytes(int T, int H, int I, int E, int k, int is_bf16) {
   const size_t eb = is_bf16 ? 2 : 4;
   const size_t head = align256(sizeof(int32_t) * (3 * static_cast<size_t>(E) + 3)) +
                       align256(sizeof(int32_t) * slots) + align256(slots * I * eb);
-  if (use_col_path(T, I, k, is_bf16)) {
+  if (use_col_path(T, H, I, E, k, is_bf16)) {
     const size_t items = (slots + 15) / 16 + (static_cast<size_t>(E) < slots ? E : slots);
     return head + align256(items * sizeof(int4));
   }
@@ -1032,7 +1048,7 @@ void forward_carve(void* ws, ForwardParams& p) {
   c += align256(sizeof(int32_t) * slots);
   p.act = c;
   c += align256(slots * p.I * eb);
-  if (use_col_path(p.T, p.I, p.k, p.is_bf16)) {
+  if (use_col_path(p.T, p.H, p.I, p.E, p.k, p.is_bf16)) {
     p.items = reinterpret_cast<int4*>(c);
     p.ys = nullptr;
   } else {
@@ -1044,7 +1060,7 @@ void forward_carve(void* ws, ForwardParams& p) {
 
 hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
   hipError_t err = hipSuccess;
-  if (use_col_path(p.T, p.I, p.k, p.is_bf16)) {
+  if (use_col_path(p.T, p.H, p.I, p.E, p.k, p.is_bf16)) {
     const ColShape cs = col_shape(p.T, p.H, p.I, p.is_bf16);
     p.zero_out = cs.ksplit == 2;
     p.item_rows = 16 * cs.mti;

@@ -43,8 +43,8 @@ def test_workspace_sizes():
     lib = L.lib()
     assert lib.acceptmoe_select_workspace_size(32, 128, 8) >= 32 * 8 * 12
     assert lib.acceptmoe_select_workspace_size(-1, 128, 8) == 0
-    # blocks of up to 256 tokens: activations (+ small lists); larger blocks also
-    # hold one fp32 output row per (token, slot)
+    # small blocks: activations (+ small lists); larger blocks also hold one fp32
+    # output row per (token, slot)
     a = lib.acceptmoe_moe_forward_workspace_size(32, 2048, 768, 128, 8, L.BF16)
     assert 32 * 8 * 768 * 2 <= a < 32 * 8 * 2048 * 4
     b = lib.acceptmoe_moe_forward_workspace_size(512, 2048, 768, 128, 8, L.BF16)
@@ -52,6 +52,37 @@ def test_workspace_sizes():
     assert lib.acceptmoe_moe_forward_workspace_size(32, 2048, 768, 128, 8, 9) == 0
     assert lib.acceptmoe_packed_weights_bytes(L.BF16, 4, 32, 64) == 4 * 32 * 64 * 2
     assert lib.acceptmoe_packed_weights_bytes(L.F32, 4, 32, 64) == 4 * 32 * 64 * 4
+
+
+# Which of the two forward paths a shape takes shows in its workspace: the
+# grouped path holds a fp32 output row per (token, slot).  The shapes were
+# measured on both paths; the rule is not one of the token count alone, and once
+# a layer's blocks have outgrown the column path larger ones stay off it, so a
+# workspace sized for the largest block serves all.
+@pytest.mark.parametrize("dtype,T,H,I,E,k,grouped", [
+    (L.BF16, 96, 2048, 768, 128, 8, False), (L.BF16, 240, 2048, 768, 128, 8, True),
+    (L.BF16, 100, 2048, 768, 128, 2, False),         # 91 us a step, 113 us grouped
+    (L.BF16, 160, 2048, 768, 128, 1, False),         # 102 / 121
+    (L.BF16, 256, 2048, 768, 16, 1, True),           # 64 / 60: 16 rows per expert
+    (L.BF16, 256, 2048, 768, 64, 8, True),           # 225 / 154
+    (L.BF16, 100, 1024, 512, 64, 8, True),           # 78 / 66
+    (L.BF16, 100, 4096, 1536, 128, 1, False),        # 202 / 221
+    (L.BF16, 70, 2048, 768, 128, 32, True),          # more slots than the column path's lists hold
+    (L.F32, 200, 2048, 768, 16, 1, False),           # 98 / 153
+    (L.F32, 195, 3584, 256, 160, 8, False),          # 266 / 302
+    (L.F32, 256, 2048, 768, 64, 8, True),            # 468 / 355
+    (L.F32, 192, 2048, 768, 64, 8, False)])
+def test_forward_path(dtype, T, H, I, E, k, grouped):
+    eb = 2 if dtype == L.BF16 else 4
+
+    def takes_grouped(t):
+        return L.lib().acceptmoe_moe_forward_workspace_size(t, H, I, E, k, dtype) >= t * k * (I * eb + H * 4)
+
+    assert takes_grouped(T) == grouped
+    paths = [takes_grouped(t) for t in range(1, 300)]
+    assert paths == sorted(paths)
+    sizes = [L.lib().acceptmoe_moe_forward_workspace_size(t, H, I, E, k, dtype) for t in range(300)]
+    assert sizes == sorted(sizes)
 
 
 def status_and_msg(rc):

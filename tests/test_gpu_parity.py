@@ -534,6 +534,61 @@ def test_forward_parity_grouped_runs(gpu, dtype, H, I):
     check_forward(got, ref, cfg.dtype, f"grouped runs H={H} I={I} {dtype}")
 
 
+# both sides of every edge between the column and the grouped path: the token
+# counts 96 / 97 (fp32 192 / 193), slots x I per down workgroup (1920, and 640 with
+# single k-steps: I = 352), 12 rows per expert, I = 256, and the most tokens and
+# slots the column path's lists hold.  Up to 256 tokens the dispatch of the
+# grouped path is one workgroup.
+@pytest.mark.parametrize("dtype,T,H,I,E,k,grouped", [
+    ("bf16", 96, 256, 256, 40, 3, False), ("bf16", 97, 256, 256, 40, 3, True),
+    ("bf16", 160, 1024, 256, 80, 6, False), ("bf16", 160, 1024, 256, 79, 6, True), ("bf16", 161, 1024, 256, 81, 6, True),
+    ("bf16", 116, 1024, 352, 24, 1, False), ("bf16", 117, 1024, 352, 24, 1, True),
+    ("bf16", 256, 128, 256, 16, 8, True), ("bf16", 256, 128, 224, 16, 8, False), ("bf16", 70, 128, 256, 40, 32, True),
+    ("f32", 192, 256, 256, 20, 3, False), ("f32", 193, 256, 256, 20, 3, True), ("f32", 240, 256, 256, 20, 1, False),
+    ("f32", 241, 256, 256, 20, 1, True), ("f32", 193, 256, 352, 20, 1, True), ("f32", 256, 256, 256, 20, 8, True)])
+def test_forward_parity_path_edges(gpu, dtype, T, H, I, E, k, grouped):
+    cfg = W.LayerConfig("edges", 1400 + T + I + E, dtype, T=T, B=1, H=H, E=E, k=k, I=I, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    ws = L.lib().acceptmoe_moe_forward_workspace_size(T, H, I, E, k, L.BF16 if dtype == "bf16" else L.F32)
+    assert (ws >= T * k * (I * cfg.wbytes + H * 4)) == grouped
+    rng = np.random.default_rng(T + I + k)
+    h32 = rng.standard_normal((T, H)).astype(np.float32)
+    idx = np.stack([rng.permutation(E)[:k] for _ in range(T)]).astype(np.int32)
+    gate = rng.random((T, k)).astype(np.float32)
+    say(f"forward edges {dtype} T={T} H={H} I={I} E={E} k={k}")
+    got, h64, (wg, wu, wd) = forward_case(cfg, idx, gate, h32)
+    ref = O.moe_forward_grouped(h64, wg, wu, wd, idx, gate, cfg.dtype)
+    check_forward(got, ref, cfg.dtype, f"edges {dtype} T={T} H={H} I={I} E={E} k={k}")
+
+
+# one layer, one workspace: blocks of the grouped path, then of the column path,
+# then larger ones again, each as in buffers of its own
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_step_across_paths(gpu, dtype):
+    cfg = W.LayerConfig("across", 1500, dtype, T=64, B=5, H=256, E=24, k=4, I=256, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    blk = W.make_block(cfg)
+    hdev, _ = hidden_for(cfg, blk.hidden)
+    weights = W.expert_weights_torch(cfg, 0, DEV)
+    rw = f32(W.router_weights(cfg))
+    layer = ops.VerifyLayer(rw, *weights, cfg.k, max_tokens=320, max_trees=5)
+    layer.fwd_ws.fill_(0xFF)
+    for B in (5, 1, 4, 2, 5):
+        T = 64 * B
+        args = (to_dev_hidden(cfg, hdev[:T]), i32(blk.parent[:T]), i32(blk.depth[:T]), f32(blk.prob[:T]),
+                blk.offsets[:B + 1])
+        say(f"step across paths {dtype} T={T}")
+        ref = ops.VerifyLayer(rw, *weights, cfg.k, max_tokens=T, max_trees=B).step(*args)
+        torch.cuda.synchronize()
+        layer.logits.fill_(float("nan"))
+        layer.out.fill_(float("nan"))
+        got = layer.step(*args)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[2], ref[2])
+        for key in ref[1]:
+            assert torch.equal(got[1][key], ref[1][key]), key
+
+
 # the most items of two M groups that a block's routing entries allow (experts
 # whose rows split into short big items: 65 = 48 + 17, 257 = 144 + 113): every
 # output run has a workgroup.  The workspace starts as NaN, so a run that nobody
