@@ -275,9 +275,10 @@ class VerifyLayer:
         return other
 
     def step(self, hidden, parent, depth, prob, tree_offsets=None, resident=None, stream=None):
-        # route(), select() and moe_forward() on the layer's own buffers: the
-        # caller's tensors are checked once and the stream looked up once (a
-        # small block's step is bound by this host work: T = 8 33.6 -> 22.4 us a step)
+        # route(), select() and moe_forward() on the layer's own buffers: every
+        # tensor is checked once, as those three check it, and the stream looked up
+        # once (a small block's step is bound by this host work: T = 8
+        # 33.6 -> 22.4 us a step)
         _need(hidden, "hidden", self.dtype, 2)
         _need(depth, "depth", torch.int32, 1)
         _need(prob, "prob", torch.float32, 1)
@@ -287,8 +288,18 @@ class VerifyLayer:
             _need(resident, "resident", torch.uint8, 1)
         T, H = hidden.shape
         offs_np, offs_ptr, B = _offsets(tree_offsets)  # offs_np: alive until the calls return
-        if H != self.H:
-            raise ValueError(f"router packed for H={self.H}, hidden has H={H}")
+        router, wgu, wd = self.router, self.wgu, self.wd
+        if not isinstance(router, PackedRouter):
+            raise TypeError("route needs the router matrix packed by pack_router_weights")
+        if not isinstance(wgu, PackedGateUp):
+            raise TypeError("w_gate_up must come from pack_gate_up_weights")
+        _need(wgu.data, "w_gate_up", self.dtype, 1)
+        _need(wd, "w_down", self.dtype, 3)
+        if router.H != H or router.E != self.E or H != self.H:
+            raise ValueError(f"router packed for H={router.H}, E={router.E}, hidden has H={H}, "
+                             f"the layer H={self.H}, E={self.E}")
+        if wgu.H != H or wd.shape != (wgu.E, H, wgu.I):
+            raise ValueError("weights must be gate/up packed from [E, I, H] stacks and down [E, H, I]")
         if T > self.max_tokens or B > self.max_trees:
             raise ValueError(f"layer holds {self.max_tokens} tokens in {self.max_trees} trees, got {T} in {B}")
         logits, outs, out = self.logits, self.sel_out, self.out
@@ -301,13 +312,13 @@ class VerifyLayer:
         s, code, hp = _stream_ptr(stream), _dtype_code(hidden), hidden.data_ptr()
         zp, ip, gp = logits.data_ptr(), outs["idx"].data_ptr(), outs["gate"].data_ptr()
         h = lib()
-        check(h.acceptmoe_route(hp, code, self.router.data.data_ptr(), T, H, self.E, zp, s))
+        check(h.acceptmoe_route(hp, code, router.data.data_ptr(), T, H, self.E, zp, s))
         check(h.acceptmoe_select(zp, _ptr(parent), depth.data_ptr(), prob.data_ptr(), offs_ptr, B, T, self.E, self.k,
                                  float(self.beta), int(self.mode), int(self.budget), int(self.removal_cap),
                                  _ptr(resident),
                                  outs["eligible"].data_ptr(), ip, gp, outs["stats"].data_ptr(),
                                  self.sel_ws.data_ptr(), self.sel_ws.numel(), s))
-        check(h.acceptmoe_moe_forward(hp, code, self.wgu.data.data_ptr(), self.wd.data_ptr(), T, H, self.I, self.E,
+        check(h.acceptmoe_moe_forward(hp, code, wgu.data.data_ptr(), wd.data_ptr(), T, H, wgu.I, wgu.E,
                                       self.k, ip, gp, out.data_ptr(), self.fwd_ws.data_ptr(), self.fwd_ws.numel(), s))
         return logits, outs, out
 
