@@ -278,7 +278,7 @@ class VerifyLayer:
         # route(), select() and moe_forward() on the layer's own buffers: every
         # tensor is checked once, as those three check it, and the stream looked up
         # once (a small block's step is bound by this host work: T = 8
-        # 33.6 -> 22.4 us a step)
+        # 33.6 -> 22.8 us a step)
         _need(hidden, "hidden", self.dtype, 2)
         _need(depth, "depth", torch.int32, 1)
         _need(prob, "prob", torch.float32, 1)
@@ -302,13 +302,12 @@ class VerifyLayer:
             raise ValueError("weights must be gate/up packed from [E, I, H] stacks and down [E, H, I]")
         if T > self.max_tokens or B > self.max_trees:
             raise ValueError(f"layer holds {self.max_tokens} tokens in {self.max_trees} trees, got {T} in {B}")
-        logits, outs, out = self.logits, self.sel_out, self.out
-        if T != self.max_tokens or B != self.max_trees:
-            logits, out = logits[:T], out[:T]
-            outs = {"eligible": outs["eligible"][:B], "idx": outs["idx"][:T], "gate": outs["gate"][:T],
-                    "stats": outs["stats"][:B]}
-        else:
-            outs = dict(outs)
+        # views, not the buffers themselves: what a caller does to their shape or
+        # autograd state does not reach the layer
+        buf = self.sel_out
+        logits, out = self.logits[:T], self.out[:T]
+        outs = {"eligible": buf["eligible"][:B], "idx": buf["idx"][:T], "gate": buf["gate"][:T],
+                "stats": buf["stats"][:B]}
         s, code, hp = _stream_ptr(stream), _dtype_code(hidden), hidden.data_ptr()
         zp, ip, gp = logits.data_ptr(), outs["idx"].data_ptr(), outs["gate"].data_ptr()
         h = lib()

@@ -97,3 +97,19 @@ def test_step_refuses_weights_that_do_not_fit(recorder, change, error):
     with pytest.raises(error):
         ly.step(*block())
     assert recorder.calls == []
+
+
+# the returned tensors are views: what a caller does to their shape or their
+# autograd state stays with the caller, at the layer's full size too
+def test_step_returns_views_of_the_buffers(recorder):
+    ly = layer()
+    logits, outs, out = ly.step(*block())
+    out.unsqueeze_(0)
+    out.requires_grad_()
+    logits.t_()
+    outs["idx"].squeeze_().unsqueeze_(2)
+    del outs["gate"]
+    logits2, outs2, out2 = ly.step(*block())
+    assert out2.shape == (T, H) and not out2.requires_grad and logits2.shape == (T, E)
+    assert outs2["idx"].shape == (T, K) and set(outs2) == {"eligible", "idx", "gate", "stats"}
+    assert out2.data_ptr() == out.data_ptr() == ly.out.data_ptr()
