@@ -33,6 +33,8 @@ def _offsets(tree_offsets):
     if tree_offsets is None:
         return None, None, 1
     a = np.ascontiguousarray(tree_offsets, dtype=np.int32)
+    if a.ndim != 1:
+        raise TypeError(f"tree_offsets must be one sequence of B + 1 ints, got shape {a.shape}")
     return a, a.ctypes.data, len(a) - 1
 
 

@@ -2,6 +2,7 @@
 layer are refused before the first of them, with the errors route() and
 moe_forward() raise.  No GPU: the library is a recorder and the tensors are host
 tensors that say they are on the device."""
+import numpy as np
 import pytest
 import torch
 
@@ -113,3 +114,14 @@ def test_step_returns_views_of_the_buffers(recorder):
     assert out2.shape == (T, H) and not out2.requires_grad and logits2.shape == (T, E)
     assert outs2["idx"].shape == (T, K) and set(outs2) == {"eligible", "idx", "gate", "stats"}
     assert out2.data_ptr() == out.data_ptr() == ly.out.data_ptr()
+
+
+@pytest.mark.parametrize("offsets", [[[0], [T]], [[0, T]], np.zeros((2, 2), np.int64), [[]]])
+def test_two_dimensional_tree_offsets_are_refused(recorder, offsets):
+    hidden, parent, depth, prob = block()
+    with pytest.raises(TypeError):
+        layer().step(hidden, parent, depth, prob, offsets)
+    for fn in (ops.select, ops.select_noalloc):
+        with pytest.raises(TypeError):
+            fn(zeros(T, E), parent, depth, prob, offsets, K)
+    assert recorder.calls == []
