@@ -368,7 +368,7 @@ def test_forward_lowest_gate_slot(gpu, name):
     check_forward(y2 - y1, ref, cfg.dtype, f"slot {j} contribution {name}")
 
 
-# T = 100 takes the column-tile down pass, T = 300 the per-slot pass + combine
+# T = 100 takes the column path (I < 256), T = 300 the grouped path
 @pytest.mark.parametrize("dtype,T", [("bf16", 100), ("f32", 100), ("bf16", 300), ("f32", 300)])
 def test_forward_parity_ragged_and_hot_expert(gpu, dtype, T):
     # T not a multiple of 16, E not a multiple of 64, one expert receiving every token
@@ -377,7 +377,7 @@ def test_forward_parity_ragged_and_hot_expert(gpu, dtype, T):
     rng = np.random.default_rng(3)
     h32 = rng.standard_normal((T, cfg.H)).astype(np.float32)
     others = np.array([e for e in range(cfg.E) if e != 7])
-    # expert 7 gets every token (several 64-token passes); the rest distinct per row
+    # expert 7 gets every token (several passes or items); the rest distinct per row
     idx = np.stack([np.concatenate([[7], rng.permutation(others)[:cfg.k - 1]]) for _ in range(T)])
     idx = idx.astype(np.int32)
     idx[5] = [3, -1, 25]                            # invalid entries are skipped
@@ -420,7 +420,7 @@ def test_forward_no_routed_expert(gpu, T):
     check_forward(out.cpu().numpy(), ref, cfg.dtype, f"routed after unrouted T={T}")
 
 
-# more tokens than a grid's y dimension holds (65,535): the per-slot path and its
+# more tokens than a grid's y dimension holds (65,535): the grouped path and its
 # combine over 65,600 tokens of a small layer
 def test_forward_parity_many_tokens(gpu):
     T = 65_600
@@ -437,7 +437,8 @@ def test_forward_parity_many_tokens(gpu):
 
 
 # forward path limits: k > 8 in the in-LDS dispatch, exactly 256 tokens / 2048
-# slots (largest column-tile block), 257 tokens (per-slot pass), E = 48
+# slots (the largest block of the column path, which a thin I stays on), 257
+# tokens (grouped path), E = 48
 @pytest.mark.parametrize("T,k,E,dtype", [(40, 32, 64, "bf16"), (37, 12, 48, "f32"), (256, 8, 64, "bf16"),
                                          (257, 8, 64, "bf16")])
 def test_forward_parity_path_limits(gpu, T, k, E, dtype):
@@ -453,11 +454,9 @@ def test_forward_parity_path_limits(gpu, T, k, E, dtype):
     check_forward(got, ref, cfg.dtype, f"limits T={T} k={k} E={E}")
 
 
-# blocks of more than 256 tokens: experts with more than 4 M-tiles of tokens run
-# their waves as 2 or 4 M groups over one weight stream.  Token counts 70, 100,
-# 130, 260 and 40 give the gate/up pass M groups of 2 x 3, 2 x 4 and 4 x 3
-# M-tiles and a 4 x 4 pass followed by a single M-tile, and the down pass 2 x 3,
-# 2 x 4 and repeated 2 x 4 passes with ragged remainders.
+# grouped path, experts of 40, 70, 100, 130 and 260 tokens: bf16 items of 3, 5 and 7
+# M-tiles, one of 130 rows in two M groups and two for 260 (144 + 116); fp32 one to
+# five items of up to 4 M-tiles each
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_forward_parity_m_groups(gpu, dtype):
     T, k, E = 300, 2, 8
@@ -632,7 +631,7 @@ def test_forward_parity_thin_shard(gpu, H, I, T, E):
     check_forward(got, ref, cfg.dtype, f"thin shard H={H} I={I}")
 
 
-# fp32 with I / 16 odd: the last gate/up tile pair is half padding (column-tile and per-slot paths)
+# fp32 with I / 16 odd: the last gate/up tile pair is half padding (column and grouped paths)
 @pytest.mark.parametrize("T", [37, 300])
 def test_forward_parity_odd_tile_count(gpu, T):
     cfg = W.LayerConfig("oddtiles", 97 + T, "f32", T=T, B=1, H=128, E=12, k=3, I=80, depth_max=6,
@@ -778,7 +777,9 @@ def test_end_to_end(gpu, name, rho):
 # ---------------------------------------------------------------------------
 # VerifyLayer.step makes the three calls itself: the same bits as route(),
 # select() and moe_forward(), at the layer's full size and below it, on another
-# stream, and larger or mistyped blocks refused before anything is launched
+# stream, and larger or mistyped blocks refused before anything is launched.
+# Each step finds its buffers poisoned, and the other stream's step gets inputs
+# that only that stream's own queue has written and is waited for alone.
 def test_step_matches_separate_calls(gpu):
     cfg = W.LayerConfig("step", 88, "bf16", T=12, B=3, H=256, E=24, k=4, I=96, depth_max=6,
                         commit_rule="depth_sibling", hidden_std=1.0)
@@ -788,20 +789,38 @@ def test_step_matches_separate_calls(gpu):
     layer = ops.VerifyLayer(f32(W.router_weights(cfg)), wg, wu, wd, cfg.k, max_tokens=36, max_trees=3, budget=9,
                             mode=L.MODE_FIXED_BUDGET)
     side = torch.cuda.Stream()
-    for B, stream in ((3, None), (1, None), (2, side)):
+    busy = torch.randn(2048, 2048, device=DEV)
+    for B, stream in ((3, None), (1, None), (2, side), (3, side)):
         T = 12 * B
         hid, par, dep, pr = (to_dev_hidden(cfg, hdev[:T]), i32(blk.parent[:T]), i32(blk.depth[:T]), f32(blk.prob[:T]))
         offs = blk.offsets[:B + 1] if B > 1 else None
         z = ops.route(hid, layer.router)
         sel = ops.select(z, par, dep, pr, offs, cfg.k, 0.5, L.MODE_FIXED_BUDGET, 9)
         y = ops.moe_forward(hid, layer.wgu, layer.wd, sel["idx"], sel["gate"])
+        for t in (layer.logits, layer.out, layer.sel_out["gate"]):
+            t.fill_(float("nan"))
+        for t in (layer.sel_ws, layer.fwd_ws, layer.sel_out["eligible"]):
+            t.fill_(0xFF)
+        for t in (layer.sel_out["idx"], layer.sel_out["stats"]):
+            t.fill_(-7)
+        late = torch.zeros_like(hid)
         torch.cuda.synchronize()
-        logits, outs, out = layer.step(hid, par, dep, pr, offs, stream=stream)
+        if stream is None:
+            logits, outs, out = layer.step(hid, par, dep, pr, offs)
+            torch.cuda.synchronize()
+        else:
+            with torch.cuda.stream(stream):
+                for _ in range(40):
+                    busy = (busy @ busy).clamp_(-1.0, 1.0)
+                late.copy_(hid)
+            logits, outs, out = layer.step(late, par, dep, pr, offs, stream=stream)
+            stream.synchronize()
+        with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream()):
+            got = [t.clone() for t in (logits, out, *(outs[key] for key in sel))]
         torch.cuda.synchronize()
         assert logits.shape == z.shape and out.shape == y.shape
-        assert torch.equal(logits, z) and torch.equal(out, y)
-        for key in sel:
-            assert torch.equal(outs[key], sel[key]), key
+        for name, t, want in zip(("logits", "out", *sel), got, (z, y, *sel.values())):
+            assert torch.equal(t, want), (name, B)
     hid, par, dep, pr = (to_dev_hidden(cfg, hdev), i32(blk.parent), i32(blk.depth), f32(blk.prob))
     with pytest.raises(ValueError):
         layer.step(torch.cat([hid, hid]), par, dep, pr)
