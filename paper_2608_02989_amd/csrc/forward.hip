@@ -27,7 +27,8 @@ namespace amoe {
 namespace {
 
 constexpr int kDispatchThreads = 1024;
-constexpr int kDispatchChunk = 256;  // nodes whose positions one dispatch workgroup writes
+constexpr int kDispatchChunk = 256;   // nodes whose positions a dispatch workgroup finds at a time
+constexpr int kDispatchMaxWgs = 256;
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -146,7 +147,13 @@ __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, cons
 
 // ---------------------------------------------------------------------------
 // dispatch of the grouped path: CSR of (expert -> slot ids in node order) and
-// the items of the grouped GEMMs.  One workgroup per kDispatchChunk nodes.
+// the items of the grouped GEMMs.  A workgroup writes the lists of
+// nodes_per_wg nodes, one chunk of kDispatchChunk after the other: one chunk up to
+// kDispatchMaxWgs of them (a workgroup per CU), more chunks beyond, because every
+// workgroup counts all rows and a second round of them would count them again
+// (whole forward of 1,048,560 nodes, H = I = 64, 64 experts, top-2: 2.4 ms, with one
+// chunk per workgroup at any size 16.1 ms; H = 64, I = 32, 512 experts, top-8: 7.2
+// and 60.7 ms).
 // Every workgroup counts all routing rows, so no workgroup waits for another:
 // its own nodes go into per-expert bitmasks, which give both their count and
 // their positions (in node order, so the result is deterministic), the nodes
@@ -156,7 +163,7 @@ __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, cons
 // expert's rows in equal runs of whole M-tiles, at most p.item_rows each.
 // ---------------------------------------------------------------------------
 template <int KMAX>
-__global__ __launch_bounds__(kDispatchThreads) void dispatch_kernel(ForwardParams p) {
+__global__ __launch_bounds__(kDispatchThreads) void dispatch_kernel(ForwardParams p, int nodes_per_wg) {
   constexpr int words = kDispatchChunk / 32;
   constexpr int kItemWave = kDispatchChunk / kWave;  // the first wave without a node of its own
   __shared__ int s_cnt[kMaxExperts];
@@ -167,21 +174,28 @@ __global__ __launch_bounds__(kDispatchThreads) void dispatch_kernel(ForwardParam
   __shared__ int s_nact;
   const int tid = threadIdx.x;
   const int E = p.E, k = p.k, T = p.T;
-  const int c0 = blockIdx.x * kDispatchChunk;  // first node of this workgroup
+  int c0 = blockIdx.x * nodes_per_wg;  // first node of the current chunk
+  const int c_end = min(T, c0 + nodes_per_wg);
   // the node whose list entries this thread writes, loaded beside the clearing
   int own[KMAX];
   uint32_t own_valid = 0u;
-  const int t_own = c0 + tid;
-  if (tid < kDispatchChunk && t_own < T)
-    own_valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(t_own) * k, k, E, own);
+  auto load_own = [&]() {
+    own_valid = 0u;
+    if (tid < kDispatchChunk && c0 + tid < c_end)
+      own_valid = load_route_row<KMAX>(p.topk_idx + static_cast<size_t>(c0 + tid) * k, k, E, own);
+  };
+  auto mark_own = [&]() {
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j)
+      if (own_valid & (1u << j)) atomicOr(&s_mask[own[j] * words + (tid >> 5)], 1u << (tid & 31));
+  };
+  load_own();
   for (int e = tid; e < E; e += kDispatchThreads) s_cnt[e] = s_before[e] = 0;
   for (int i = tid; i < E * words; i += kDispatchThreads) s_mask[i] = 0u;
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j)
-    if (own_valid & (1u << j)) atomicOr(&s_mask[own[j] * words + (tid >> 5)], 1u << (tid & 31));
-  // the other nodes: i counts the T nodes without the workgroup's own
-  const int n_own = min(kDispatchChunk, T - c0);
+  mark_own();
+  // the other nodes: i counts the T nodes without the first chunk
+  const int n_own = min(kDispatchChunk, c_end - c0);
   for (int i = tid; i < T - n_own; i += kDispatchThreads) {
     const int t = i < c0 ? i : i + n_own;
     int* cnt = i < c0 ? s_before : s_cnt;
@@ -204,17 +218,36 @@ __global__ __launch_bounds__(kDispatchThreads) void dispatch_kernel(ForwardParam
     if (tid == 0) s_nact = na;
   }
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (own_valid & (1u << j)) {
-      const uint32_t* m = s_mask + own[j] * words;
-      int pos = s_off[own[j]] + s_before[own[j]] + __popc(m[tid >> 5] & ((1u << (tid & 31)) - 1u));
-#pragma unroll
-      for (int w = 0; w < words; ++w) pos += w < (tid >> 5) ? __popc(m[w]) : 0;
-      p.ent_slot[pos] = t_own * k + j;
-    }
-  }
   if (blockIdx.x == 0 && wave_id() == kItemWave) write_grouped_items(p, s_cnt, s_off, s_active, s_nact, lane_id());
+  for (;;) {
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) {
+      if (own_valid & (1u << j)) {
+        const uint32_t* m = s_mask + own[j] * words;
+        int pos = s_off[own[j]] + s_before[own[j]] + __popc(m[tid >> 5] & ((1u << (tid & 31)) - 1u));
+#pragma unroll
+        for (int w = 0; w < words; ++w) pos += w < (tid >> 5) ? __popc(m[w]) : 0;
+        p.ent_slot[pos] = (c0 + tid) * k + j;
+      }
+    }
+    c0 += kDispatchChunk;
+    if (c0 >= c_end) break;
+    __syncthreads();
+    // the finished chunk's nodes come before those of the next
+    for (int e = tid; e < E; e += kDispatchThreads) {
+      int c = 0;
+#pragma unroll
+      for (int w = 0; w < words; ++w) {
+        c += __popc(s_mask[e * words + w]);
+        s_mask[e * words + w] = 0u;
+      }
+      s_before[e] += c;
+    }
+    load_own();
+    __syncthreads();
+    mark_own();
+    __syncthreads();
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1077,12 +1110,14 @@ hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
   p.item_rows = grouped_item_rows(p.is_bf16 ? 2 : 4);
   p.big_rows = grouped_big_rows(p.is_bf16 ? 2 : 4);
   const int chunks = (p.T + kDispatchChunk - 1) / kDispatchChunk;
+  const int per_wg = (chunks + kDispatchMaxWgs - 1) / kDispatchMaxWgs * kDispatchChunk;
+  const int wgs = (p.T + per_wg - 1) / per_wg;
   if (p.k <= 8)
-    dispatch_kernel<8><<<chunks, kDispatchThreads, 0, stream>>>(p);
+    dispatch_kernel<8><<<wgs, kDispatchThreads, 0, stream>>>(p, per_wg);
   else if (p.k <= 16)
-    dispatch_kernel<16><<<chunks, kDispatchThreads, 0, stream>>>(p);
+    dispatch_kernel<16><<<wgs, kDispatchThreads, 0, stream>>>(p, per_wg);
   else
-    dispatch_kernel<kMaxTopK><<<chunks, kDispatchThreads, 0, stream>>>(p);
+    dispatch_kernel<kMaxTopK><<<wgs, kDispatchThreads, 0, stream>>>(p, per_wg);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   err = launch_grouped(p, max_grouped_items(p.T, p.E, p.k, p.is_bf16), stream);

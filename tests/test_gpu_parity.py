@@ -421,9 +421,11 @@ def test_forward_no_routed_expert(gpu, T):
 
 
 # more tokens than a grid's y dimension holds (65,535): the grouped path and its
-# combine over 65,600 tokens of a small layer
-def test_forward_parity_many_tokens(gpu):
-    T = 65_600
+# combine over 65,600 tokens of a small layer.  Above 65,536 tokens a workgroup of
+# the dispatch does two chunks of 256; the last one gets 64 tokens, and 256 + 208
+# at 66,000
+@pytest.mark.parametrize("T", [65_600, 66_000])
+def test_forward_parity_many_tokens(gpu, T):
     cfg = W.LayerConfig("many", 99, "bf16", T=T, B=1, H=64, E=6, k=2, I=32, depth_max=6,
                         commit_rule="depth_sibling", hidden_std=1.0)
     rng = np.random.default_rng(65_600)
