@@ -120,10 +120,9 @@ __device__ __forceinline__ void write_down_items(const ForwardParams& p, const i
   if (tid == 0) *p.n_items = base;
 }
 
-// Items (expert, first CSR row, rows) of the grouped GEMMs: each active
-// expert's rows in equal runs of whole M-tiles, at most p.item_rows rows each,
-// and their count (one wave).  Items of more than p.big_rows rows, which take
-// longest, come first (their count goes to n_active), each group in
+// Items (expert, first CSR row, rows) of the grouped GEMMs, as split_rows cuts
+// each active expert's rows, and their count (one wave).  The big items, which
+// take longest, come first (their count goes to n_active), each group in
 // active-expert order.
 __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, const int* cnt, const int* off,
                                                     const int* active, int na, int tid) {
@@ -133,11 +132,11 @@ __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, cons
       const int a = a0 + tid;
       const int e = a < na ? active[a] : 0;
       const int c = a < na ? cnt[e] : 0;
-      const ItemSplit sp = split_rows(c, p.item_rows, p.big_rows);
-      const int n = sp.big == (big != 0) ? sp.items : 0;
+      const ItemSplit sp = split_rows(c, p.is_bf16 ? 2 : 4);
+      const int first = big != 0 ? 0 : sp.big, n = (big != 0 ? sp.big : sp.items) - first;
       const int incl = wave_incl_scan_i32(n);
-      for (int m = 0; m < n; ++m)
-        p.items[base + incl - n + m] = make_int4(e, off[e] + sp.rows * m, min(sp.rows, c - sp.rows * m), 0);
+      for (int m = first; m < first + n; ++m)
+        p.items[base + incl - n + m - first] = make_int4(e, off[e] + sp.rows * m, min(sp.rows, c - sp.rows * m), 0);
       base += lane_value(incl, kWave - 1);
     }
     if (big != 0 && tid == 0) *p.n_active = base;
@@ -159,8 +158,7 @@ __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, cons
 // their positions (in node order, so the result is deterministic), the nodes
 // before and after into counters.  That is one LDS atomic per slot; a wave's
 // atomics on a popular expert run one after the other and bound the kernel.
-// A wave beyond those that write the lists writes the items (workgroup 0): an
-// expert's rows in equal runs of whole M-tiles, at most p.item_rows each.
+// A wave beyond those that write the lists writes the items (workgroup 0).
 // ---------------------------------------------------------------------------
 template <int KMAX>
 __global__ __launch_bounds__(kDispatchThreads) void dispatch_kernel(ForwardParams p, int nodes_per_wg) {
@@ -1107,8 +1105,6 @@ hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
     if (err != hipSuccess) return err;
     return p.is_bf16 ? launch_down_col<Bf16Path>(p, cs, stream) : launch_down_col<F32Path>(p, cs, stream);
   }
-  p.item_rows = grouped_item_rows(p.is_bf16 ? 2 : 4);
-  p.big_rows = grouped_big_rows(p.is_bf16 ? 2 : 4);
   const int chunks = (p.T + kDispatchChunk - 1) / kDispatchChunk;
   const int per_wg = (chunks + kDispatchMaxWgs - 1) / kDispatchMaxWgs * kDispatchChunk;
   const int wgs = (p.T + per_wg - 1) / per_wg;

@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 // slower at 8 x 64 (H = 4096).
 template <class P, Grouped F>
 hipError_t launch_grouped_pass(const ForwardParams& p, int max_items, int nblocks, hipStream_t stream) {
-  const long long grid = grouped_workgroups(p.T * p.k, max_items, p.big_rows, nblocks);
+  const long long grid = grouped_workgroups(p.T * p.k, max_items, grouped_big_rows(P::kElemBytes), nblocks);
   // far beyond what the slot rows of one device's memory allow
   if (grid > 0x7fffffffll) return hipErrorInvalidValue;
   grouped_kernel<P, F><<<static_cast<unsigned>(grid), 256, 0, stream>>>(p, nblocks);

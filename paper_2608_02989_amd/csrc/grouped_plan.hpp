@@ -12,18 +12,23 @@ constexpr int grouped_tile_m2(int elem_bytes) { return elem_bytes == 2 ? 6 : 2; 
 constexpr int grouped_item_rows(int elem_bytes) { return 2 * 16 * grouped_tile_m2(elem_bytes); }
 constexpr int grouped_big_rows(int elem_bytes) { return 16 * grouped_tile_m(elem_bytes); }
 
-// An expert's `count` rows in equal runs of whole M-tiles, at most item_rows
-// each: items m = 0 .. items - 1 of min(rows, count - rows m) rows.  All of them
-// are big or none, whatever the last one holds.
+// An expert's `count` rows in items m = 0 .. items - 1 of min(rows, count - rows m)
+// rows, the first `big` of which are big.  bf16: equal runs of whole M-tiles, at
+// most item_rows each, all big or none, whatever the last one holds.  fp32, whose
+// time is the M-tiles multiplied (a big item's four, also for fewer rows): full
+// items and the rest, 65 rows in 64 + 1 rather than 48 + 17 (16 experts, top-1,
+// 1075 tokens, H = 1088, I = 1760: 323 -> 221 us a step).
 struct ItemSplit {
-  int rows, items;
-  bool big;
+  int rows, items, big;
 };
-constexpr ItemSplit split_rows(int count, int item_rows, int big_rows) {
-  const int tiles = (count + 15) / 16;
+constexpr ItemSplit split_rows(int count, int elem_bytes) {
+  const int item_rows = grouped_item_rows(elem_bytes), big_rows = grouped_big_rows(elem_bytes);
   const int most = (count + item_rows - 1) / item_rows;
+  if (elem_bytes == 4) return {item_rows, most, count / item_rows + (count % item_rows > big_rows ? 1 : 0)};
+  const int tiles = (count + 15) / 16;
   const int rows = most > 0 ? 16 * ((tiles + most - 1) / most) : 16;
-  return {rows, (count + rows - 1) / rows, (rows < count ? rows : count) > big_rows};
+  const int items = (count + rows - 1) / rows;
+  return {rows, items, (rows < count ? rows : count) > big_rows ? items : 0};
 }
 
 // most items of a block of `slots` routing entries: one per active expert and
@@ -76,9 +81,10 @@ constexpr GroupedShare grouped_share(int block, int n_items, int n_big, int nblo
 // Workgroups that cover every item's nblocks runs for any routing of `slots`
 // entries: per XCD one whole run's workgroups for each item and as many again
 // for the big items and for the last ones.  There are at most slots / big_rows
-// big items: runs of big_rows / 16 + 1 M-tiles or more in each of n items make
-// more than n big_rows / 16 M-tiles, so the expert has at least n big_rows rows
-// although its last item may hold fewer (257 rows: 144 + 113).
+// big items.  fp32: each holds more than big_rows rows.  bf16: runs of
+// big_rows / 16 + 1 M-tiles or more in each of n items make more than
+// n big_rows / 16 M-tiles, so the expert has at least n big_rows rows although its
+// last item may hold fewer (257 rows: 144 + 113).
 constexpr long long grouped_workgroups(int slots, int max_items, int big_rows, int nblocks) {
   const int n_split = grouped_split_items(nblocks);
   const int max_big = slots / big_rows;

@@ -79,7 +79,7 @@ struct ForwardParams {
   int32_t* cnt;       // [E]
   int32_t* off;       // [E + 1]
   int32_t* active;    // [E]
-  int32_t* n_active;  // [1] routed experts (column path) or items above big_rows (grouped path)
+  int32_t* n_active;  // [1] routed experts (column path) or big items (grouped path)
   int32_t* ent_slot;  // [T * k] slot ids grouped by expert, token order
   void* act;          // [T * k, I] bf16 or fp32
   float* ys;          // [T * k, H] gate-weighted expert outputs (grouped path only)
@@ -87,8 +87,7 @@ struct ForwardParams {
   int32_t* n_items;   // [1]
   int T, H, I, E, k, is_bf16;
   int zero_out;       // gate/up pass clears out (the down pass then adds two halves into it)
-  int item_rows;      // most rows of an item (16 per M-tile)
-  int big_rows;       // items of the grouped GEMMs above this size take two M groups and half runs
+  int item_rows;      // most rows of a column-tile down item (16 per M-tile)
 };
 
 // grouped GEMMs of larger blocks (grouped.hip), both passes

@@ -591,7 +591,7 @@ def test_step_across_paths(gpu, dtype):
 
 
 # the most items of two M groups that a block's routing entries allow (experts
-# whose rows split into short big items: 65 = 48 + 17, 257 = 144 + 113): every
+# whose rows split into short big items: bf16 257 = 144 + 113): every
 # output run has a workgroup.  The workspace starts as NaN, so a run that nobody
 # computes shows.
 @pytest.mark.parametrize("dtype,T,k,groups", [("f32", 400, 8, [(49, 65), (15, 1)]),

@@ -24,16 +24,18 @@ static bool covered(const std::vector<int>& counts, int eb, int nblocks) {
   int slots = 0, n_items = 0, n_big = 0;
   for (int c : counts) {
     slots += c;
-    const ItemSplit sp = split_rows(c, item_rows, big_rows);
-    int left = c;
+    const ItemSplit sp = split_rows(c, eb);
+    int left = c, multiplied = 0;  // M-tiles: a big item of fp32 multiplies four
+    if (sp.big < 0 || sp.big > sp.items) return false;
     for (int m = 0; m < sp.items; ++m) {
       const int rows = sp.rows < left ? sp.rows : left;
-      if (rows < 1 || rows > item_rows || (!sp.big && rows > big_rows)) return false;
+      if (rows < 1 || rows > item_rows || (m >= sp.big && rows > big_rows)) return false;
       left -= rows;
+      multiplied += m < sp.big ? grouped_item_rows(eb) / 16 : (rows + 15) / 16;
     }
-    if (left != 0) return false;
+    if (left != 0 || (eb == 4 && multiplied > (c + 15) / 16 + 1)) return false;
     n_items += sp.items;
-    n_big += sp.big ? sp.items : 0;
+    n_big += sp.big;
   }
   const int max_items = grouped_max_items(slots, static_cast<int>(counts.size()), item_rows);
   if (n_items > max_items) return false;
@@ -64,7 +66,7 @@ int main() {
   // m experts with `a` rows and s with `b`
   for (int eb : {2, 4}) {
     const std::vector<int> big = eb == 2 ? std::vector<int>{129, 193, 257, 384, 385, 386, 577}
-                                         : std::vector<int>{33, 49, 65, 97, 129, 193};
+                                         : std::vector<int>{32, 33, 49, 64, 65, 97, 129, 193};
     for (int a : big)
       for (int b : {1, 16})
         for (int m : {0, 1, 3, 11, 20, 21, 43, 49, 64, 96, 128, 500})
@@ -77,14 +79,14 @@ int main() {
                 bad += check(counts, eb, nb, "pair", a, m, b, s);
               }
     // a longer sweep of the counts with the fewest rows per item
-    const int a = eb == 2 ? 385 : 65;
-    for (int m = 1; m <= 60; ++m)
-      for (int s = 0; s <= 40; ++s)
-        for (int nb : {8, 16}) {
-          std::vector<int> counts(m, a);
-          counts.insert(counts.end(), s, 1);
-          bad += check(counts, eb, nb, "sweep", a, m, 1, s);
-        }
+    for (int a : eb == 2 ? std::vector<int>{257, 385} : std::vector<int>{33, 65, 97})
+      for (int m = 1; m <= 60; ++m)
+        for (int s = 0; s <= 40; ++s)
+          for (int nb : {8, 16}) {
+            std::vector<int> counts(m, a);
+            counts.insert(counts.end(), s, 1);
+            bad += check(counts, eb, nb, "sweep", a, m, 1, s);
+          }
     std::mt19937 rng(7);
     for (int i = 0; i < 2000; ++i) {
       std::vector<int> counts(1 + rng() % 200);
