@@ -968,13 +968,14 @@ ColShape col_shape(int T, int H, int I, int is_bf16) {
 //                        E = 16, k = 1: T = 100 46 / 57, T = 256 64 / 60
 //   H = 1024, I = 512    E = 64: k = 1, T = 100 39 / 45; k = 8, T = 100 78 / 66
 //   H = 4096, I = 1536   E = 128: k = 1, T = 100 202 / 221; k = 8, T = 256 822 / 764
-//   fp32, H = 2048, I = 768   E = 16, k = 1, T = 200 98 / 153; E = 64, k = 8, T = 256 468 / 355
-//   fp32, H = 3584, I = 256   E = 160, k = 8, T = 195 266 / 302
+//   fp32, H = 2048, I = 768   E = 64: k = 1, T = 200 162 / 197; k = 8, T = 256 456 / 329
+//   fp32, H = 3584, I = 256   E = 160, k = 8, T = 195 262 / 285
 // and below 96 tokens, E = 128, k = 8: H = 2048, I = 768, T = 72 117 / 128, T = 96
 // 130 / 134; H = 4096, I = 1536, T = 72 323 / 330, T = 96 353 / 349.
-// Over 789 (fp32: 308) layers and blocks of 97 (193) to 256 tokens, drawn and on a
-// grid of H, I, E and k, this choice is 0.24 % (0.7 %) behind the faster path on
-// average; the grouped path throughout is 1.3 % (3.7 %) behind.
+// Over 789 (fp32: 448) layers and blocks of 97 (193) to 256 tokens, drawn and on a
+// grid of H, I, E and k, this choice is 0.24 % (0.8 %) behind the faster path on
+// average and in fp32 at most 8 % behind the column path; the grouped path
+// throughout is 1.3 % (1.2 %) behind, up to 38 % (39 %).
 bool use_col_path(int T, int H, int I, int E, int k, int is_bf16) {
   const long long slots = static_cast<long long>(T) * k;
   if (T > kColMaxT || T > kSelfMaxT || slots > kColMaxSlots || slots > kSelfMaxSlots) return false;

@@ -55,7 +55,7 @@ constexpr int kGrpMaxRows = grouped_item_rows(P::kElemBytes);
 // i + 2 and of the weights of stage i + 1 are issued, then stage i is
 // multiplied.  The row loads are issued before the weights of the same
 // round, so waiting for them leaves the weight stream in flight.
-template <class P, int MT, int MG, int FR>
+template <class P, int MT, int MG, int FR, int KS>
 __device__ __forceinline__ void grouped_product(const uint4* const (&w)[FR], const int (&wbytes)[FR],
                                                 int wstride, const uint4* const (&xrow)[(MG * MT + 1) / 2], int KC,
                                                 int mt0, uint4* lds, floatx4 (&acc)[FR][MT]) {
@@ -72,9 +72,11 @@ __device__ __forceinline__ void grouped_product(const uint4* const (&w)[FR], con
   const int dst = (piece >> 2) * kChunk + (srow >> 4) * kWave + (piece & 3) * 16 + ((srow & 15) ^ (2 * piece));
   const int src0 = g * 16 + (r ^ (2 * g));
   const int src1 = g * 16 + (r ^ (2 * (g + 4)));
+  constexpr int kMine = kGrpStage / KS;  // chunks of a stage that this wave multiplies
+  const int part = KS == 1 ? 0 : (wave_id() & 1);
   const int nst = (KC + kGrpStage - 1) / kGrpStage;
   uint4 ra[kLoads];
-  uint4 wb[2][kGrpStage][FR];
+  uint4 wb[2][kMine][FR];
   auto load_rows = [&](int st) {
     const int kc = min(min(st, nst - 1) * kGrpStage + (piece >> 2), KC - 1);  // in range; see store_rows
 #pragma unroll
@@ -85,19 +87,20 @@ __device__ __forceinline__ void grouped_product(const uint4* const (&w)[FR], con
 #pragma unroll
     for (int s = 0; s < kLoads; ++s) lds[buf * kBuf + s * 2 * kWave + dst] = in ? ra[s] : make_uint4(0u, 0u, 0u, 0u);
   };
-  auto load_w = [&](int st, uint4 (&v)[kGrpStage][FR]) {
+  auto load_w = [&](int st, uint4 (&v)[kMine][FR]) {
 #pragma unroll
-    for (int u = 0; u < kGrpStage; ++u)
+    for (int u = 0; u < kMine; ++u)
 #pragma unroll
       for (int f = 0; f < FR; ++f)
-        v[u][f] = load_weight<MG == 1 ? kPolicyStream : kPolicyPlain>(w[f], wbytes[f], (st * kGrpStage + u) * wstride + lane);
+        v[u][f] = load_weight<MG == 1 ? kPolicyStream : kPolicyPlain>(w[f], wbytes[f], (st * kGrpStage + part + u) * wstride + lane);
   };
-  auto multiply = [&](int buf, const uint4 (&v)[kGrpStage][FR], floatx4 (&a)[FR][MT]) {
+  auto multiply = [&](int buf, const uint4 (&v)[kMine][FR], floatx4 (&a)[FR][MT]) {
 #pragma unroll
-    for (int u = 0; u < kGrpStage; ++u) {
+    for (int u = 0; u < kMine; ++u) {
+      const int src = (part + u) * kChunk + (part + u != 0 ? src1 : src0);
       uint4 x[MT];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) x[mt] = lds[buf * kBuf + u * kChunk + (mt0 + mt) * kWave + (u ? src1 : src0)];
+      for (int mt = 0; mt < MT; ++mt) x[mt] = lds[buf * kBuf + (mt0 + mt) * kWave + src];
 #pragma unroll
       for (int f = 0; f < FR; ++f)
 #pragma unroll
@@ -121,7 +124,7 @@ __device__ __forceinline__ void grouped_product(const uint4* const (&w)[FR], con
   if constexpr (P::kElemBytes == 4) {
     // fp32 products: sums of 16 chunks, then the sums (shorter chains of
     // roundings than one running sum over K)
-    constexpr int kFlush = 8;  // stages
+    constexpr int kFlush = 8 * KS;  // stages
     floatx4 part[FR][MT];
 #pragma unroll
     for (int f = 0; f < FR; ++f)
@@ -169,8 +172,9 @@ constexpr int kGrpLds = 2 * kGrpStage * (2 * kGrpTileM2<P> + 1) / 2 * 2 * kWave;
 
 // MT M-tiles per wave, FR weight fragments.  MG = 2: the item has 2 MT M-tiles
 // and the four waves are two M groups over half as many output tiles.  MG = 2
-// or FR = 2: `run` counts half runs.
-template <class P, Grouped F, int MT, int MG, int FR>
+// or FR = 2: `run` counts half runs.  KS = 2 (with FR = 2): two waves share a
+// tile, each over every other K chunk, and `run` counts quarter runs.
+template <class P, Grouped F, int MT, int MG, int FR, int KS = 1>
 __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int row0, int rows, int run, uint4* lds,
                                              GroupedRows<P>& gr) {
   constexpr int kLoads = (MG * MT + 1) / 2;
@@ -186,7 +190,7 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
   const int rowq = K * P::kElemBytes / 16;
   const int ntiles = (F == Grouped::GateUp ? p.I : p.H) / 16;
   const int mt0 = MG == 1 ? 0 : (wave & 1) * MT;  // this wave's first M-tile
-  const int tile0 = (run * (4 / MG) + wave / MG) * kTiles;
+  const int tile0 = (run * (4 / (MG * KS)) + wave / (MG * KS)) * kTiles;
 
   const uint4* w[FR];
   int wbytes[FR];
@@ -235,7 +239,30 @@ __device__ __forceinline__ void grouped_item(const ForwardParams& p, int e, int 
   for (int f = 0; f < FR; ++f)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[f][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  grouped_product<P, MT, MG, FR>(w, wbytes, wstride, xrow, KC, mt0, lds, acc);
+  grouped_product<P, MT, MG, FR, KS>(w, wbytes, wstride, xrow, KC, mt0, lds, acc);
+  if constexpr (KS == 2) {
+    static_assert(MG == 1 && 2 * FR * MT * kWave <= kGrpLds<P>, "the odd chunks' sums of two tile groups fit");
+    floatx4* red = reinterpret_cast<floatx4*>(lds) + (wave / 2) * FR * MT * kWave + lane;
+    if (wave & 1) {
+#pragma unroll
+      for (int f = 0; f < FR; ++f)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) red[(f * MT + mt) * kWave] = acc[f][mt];
+    }
+    __syncthreads();
+    if (!(wave & 1)) {
+#pragma unroll
+      for (int f = 0; f < FR; ++f)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const floatx4 v = red[(f * MT + mt) * kWave];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[f][mt][q] += v[q];
+        }
+    }
+    __syncthreads();
+    if (wave & 1) return;  // no barrier follows
+  }
 
   // Lane (r, g) holds rows 4g .. 4g + 3 of column r of each tile.  Each M-tile
   // goes through this wave's part of the LDS, so the rows leave in 16-byte
@@ -304,6 +331,16 @@ __device__ __forceinline__ void grouped_small(const ForwardParams& p, int e, int
   }
 }
 
+// A quarter run of an fp32 item (see grouped_kernel).
+template <class P, Grouped F>
+__device__ __forceinline__ void grouped_quarter(const ForwardParams& p, int e, int row0, int rows, int run, uint4* lds,
+                                                GroupedRows<P>& gr) {
+  if (rows <= 16) grouped_item<P, F, 1, 1, 2, 2>(p, e, row0, rows, run, lds, gr);
+  else if (rows <= 32) grouped_item<P, F, 2, 1, 2, 2>(p, e, row0, rows, run, lds, gr);
+  else if (rows <= 48) grouped_item<P, F, 3, 1, 2, 2>(p, e, row0, rows, run, lds, gr);
+  else grouped_item<P, F, 4, 1, 2, 2>(p, e, row0, rows, run, lds, gr);
+}
+
 // Items come in groups of the workgroups that share one item's rows, group
 // after group round-robin over the XCDs (workgroup b runs on XCD b % 8), so
 // the rows are read from one XCD's L2.  An item of more than kGrpTileM M-tiles
@@ -325,21 +362,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   __shared__ uint4 lds[kGrpLds<P>];
   __shared__ GroupedRows<P> gr;
   const int n_items = *p.n_items, n_big = *p.n_active;
-  const GroupedShare sh = grouped_share(blockIdx.x, n_items, n_big, nblocks);
+  const GroupedShare sh = grouped_share(blockIdx.x, n_items, n_big, nblocks, P::kElemBytes);
   if (sh.item >= n_items) return;
   const int4 d = p.items[sh.item];
   const int run = __builtin_amdgcn_readfirstlane(sh.run);  // without this the gate/up kernel spills 65 registers, not 6
   const int e = __builtin_amdgcn_readfirstlane(d.x);
   const int row0 = __builtin_amdgcn_readfirstlane(d.y);
   const int rows = __builtin_amdgcn_readfirstlane(d.z);
+  if constexpr (P::kElemBytes == 4) {
+    if (sh.parts == 4) {
+      grouped_quarter<P, F>(p, e, row0, rows, run, lds, gr);
+      return;
+    }
+  }
   if (sh.item >= n_big) {
-    if (sh.half) grouped_small<P, F, 2>(p, e, row0, rows, run, lds, gr);
+    if (sh.parts == 2) grouped_small<P, F, 2>(p, e, row0, rows, run, lds, gr);
     else grouped_small<P, F, 4>(p, e, row0, rows, run, lds, gr);
   } else if constexpr (kGrpTileM<P> > 2) {
     if (rows <= 160) grouped_item<P, F, 5, 2, 4>(p, e, row0, rows, run, lds, gr);
     else grouped_item<P, F, 6, 2, 4>(p, e, row0, rows, run, lds, gr);
   } else {
-    grouped_item<P, F, 2, 2, 4>(p, e, row0, rows, run, lds, gr);
+    // three M-tiles in a half run of narrower waves rather than four
+    if (rows <= 48) grouped_item<P, F, 3, 1, 2>(p, e, row0, rows, run, lds, gr);
+    else grouped_item<P, F, 2, 2, 4>(p, e, row0, rows, run, lds, gr);
   }
 }
 
@@ -347,7 +392,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 // slower at 8 x 64 (H = 4096).
 template <class P, Grouped F>
 hipError_t launch_grouped_pass(const ForwardParams& p, int max_items, int nblocks, hipStream_t stream) {
-  const long long grid = grouped_workgroups(p.T * p.k, max_items, grouped_big_rows(P::kElemBytes), nblocks);
+  const long long grid = grouped_workgroups(p.T * p.k, max_items, nblocks, P::kElemBytes);
   // far beyond what the slot rows of one device's memory allow
   if (grid > 0x7fffffffll) return hipErrorInvalidValue;
   grouped_kernel<P, F><<<static_cast<unsigned>(grid), 256, 0, stream>>>(p, nblocks);

@@ -46,26 +46,39 @@ constexpr int grouped_split_items(int nblocks) {
   return (kHalfRuns / 2 + nblocks - 1) / nblocks;
 }
 
-// Workgroup `block`'s share: output run (or half run) `run` of an item; nothing
-// if item >= n_items.  The n_big big items come first and take half runs, as do
+// fp32: all items take quarter runs, whose waves share the K chunks, while their
+// half runs are no more than this, one per CU: fp32 products take a wave so long
+// that the idle CUs cost more than the rows staged twice as often.  Drawn blocks of
+// 193 to 1600 tokens, top-1 and top-2 mostly: 8 % faster than without (twice as
+// many 6 %, half as many 7 %), 360 tokens, 32 experts, top-2 (H = 3424, I = 224)
+// 210 -> 150 us a step.
+constexpr int kQuarterHalves = 256;
+constexpr bool grouped_quarters(int n_items, int nblocks, int elem_bytes) {
+  return elem_bytes == 4 && n_items <= kQuarterHalves / (2 * nblocks);
+}
+
+// Workgroup `block`'s share: output run `run` of the `parts` x nblocks that an
+// item's runs are cut into; nothing if item >= n_items.  The n_big big items come first and take half runs, as do
 // the last ones.  The items go round-robin over the XCDs (workgroup b
 // runs on XCD b % 8), all runs of one on the same XCD.
 struct GroupedShare {
-  int item, run;
-  bool half;
+  int item, run, parts;
 };
-constexpr GroupedShare grouped_share(int block, int n_items, int n_big, int nblocks) {
-  const int n_split = grouped_split_items(nblocks);
+constexpr GroupedShare grouped_share(int block, int n_items, int n_big, int nblocks, int elem_bytes) {
   const int xcd = block % 8;
+  if (grouped_quarters(n_items, nblocks, elem_bytes)) {
+    const int slot = block / 8, item = slot / (4 * nblocks);
+    return {item * 8 + xcd, slot - item * 4 * nblocks, 4};
+  }
+  const int n_split = grouped_split_items(nblocks);
   const int n_whole = n_big > n_items - n_split ? n_big : n_items - n_split;  // items [n_big, n_whole) take whole runs
   const int big = (n_big + 7 - xcd) / 8, whole = (n_whole + 7 - xcd) / 8;      // of the first n items on this XCD
-  int slot = block / 8, item = 0;
-  bool half = true;
+  int slot = block / 8, item = 0, parts = 2;
   if (slot < 2 * nblocks * big) {
     item = slot / (2 * nblocks);
     slot -= item * 2 * nblocks;
   } else if (slot -= 2 * nblocks * big; slot < nblocks * (whole - big)) {
-    half = false;
+    parts = 1;
     item = slot / nblocks;
     slot -= item * nblocks;
     item += big;
@@ -75,7 +88,7 @@ constexpr GroupedShare grouped_share(int block, int n_items, int n_big, int nblo
     slot -= item * 2 * nblocks;
     item += whole;
   }
-  return {item * 8 + xcd, slot, half};
+  return {item * 8 + xcd, slot, parts};
 }
 
 // Workgroups that cover every item's nblocks runs for any routing of `slots`
@@ -85,11 +98,13 @@ constexpr GroupedShare grouped_share(int block, int n_items, int n_big, int nblo
 // big_rows / 16 + 1 M-tiles or more in each of n items make more than
 // n big_rows / 16 M-tiles, so the expert has at least n big_rows rows although its
 // last item may hold fewer (257 rows: 144 + 113).
-constexpr long long grouped_workgroups(int slots, int max_items, int big_rows, int nblocks) {
+constexpr long long grouped_workgroups(int slots, int max_items, int nblocks, int elem_bytes) {
   const int n_split = grouped_split_items(nblocks);
-  const int max_big = slots / big_rows;
+  const int max_big = slots / grouped_big_rows(elem_bytes);
   const long long groups = (max_items + 7) / 8 + (max_big + 7) / 8 + ((n_split < max_items ? n_split : max_items) + 7) / 8;
-  return 8 * groups * nblocks;
+  const int most_q = kQuarterHalves / (2 * nblocks);  // items in quarter runs
+  const long long quarters = grouped_quarters(1, nblocks, elem_bytes) ? 4 * (((most_q < max_items ? most_q : max_items) + 7) / 8) : 0;
+  return 8 * (groups > quarters ? groups : quarters) * nblocks;
 }
 
 }  // namespace amoe

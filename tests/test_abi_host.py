@@ -68,9 +68,9 @@ def test_workspace_sizes():
     (L.BF16, 100, 1024, 512, 64, 8, True),           # 78 / 66
     (L.BF16, 100, 4096, 1536, 128, 1, False),        # 202 / 221
     (L.BF16, 70, 2048, 768, 128, 32, True),          # more slots than the column path's lists hold
-    (L.F32, 200, 2048, 768, 16, 1, False),           # 98 / 153
-    (L.F32, 195, 3584, 256, 160, 8, False),          # 266 / 302
-    (L.F32, 256, 2048, 768, 64, 8, True),            # 468 / 355
+    (L.F32, 200, 2048, 768, 64, 1, False),           # 162 / 197
+    (L.F32, 195, 3584, 256, 160, 8, False),          # 262 / 285
+    (L.F32, 256, 2048, 768, 64, 8, True),            # 456 / 329
     (L.F32, 192, 2048, 768, 64, 8, False)])
 def test_forward_path(dtype, T, H, I, E, k, grouped):
     eb = 2 if dtype == L.BF16 else 4

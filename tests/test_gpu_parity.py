@@ -516,6 +516,27 @@ def test_forward_parity_grouped_edges(gpu, dtype, T, counts):
     check_forward(got, ref, cfg.dtype, f"grouped edges T={T} {dtype}")
 
 
+# fp32: quarter runs up to 128 items of one run each, half runs from 129, whole runs
+# for items before the last 256; experts at the edges of the M-tiles (1 to 4) and of
+# the split into 64 rows and a rest, 9 and 7 K chunks, 9 tiles of H and 7 of I, which
+# end inside a quarter and a half run
+@pytest.mark.parametrize("singles", [105, 106, 300])
+def test_forward_parity_fp32_runs(gpu, singles):
+    counts = [1, 16, 17, 32, 33, 48, 49, 64, 65, 96, 97, 112, 113, 128, 129] + [1] * singles
+    T, k, E = 400, 4, len(counts)
+    cfg = W.LayerConfig("fp32runs", 990 + singles, "f32", T=T, B=1, H=144, E=E, k=k, I=112, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    flat = np.full(T * k, -1, np.int32)
+    flat[:sum(counts)] = np.repeat(np.arange(E), counts)
+    idx = np.ascontiguousarray(flat.reshape(k, T).T)  # an expert's rows follow each other, so no token repeats one
+    rng = np.random.default_rng(singles)
+    h32 = rng.standard_normal((T, cfg.H)).astype(np.float32)
+    gate = rng.random((T, k)).astype(np.float32)
+    got, h64, (wg, wu, wd) = forward_case(cfg, idx, gate, h32)
+    ref = O.moe_forward_grouped(h64, wg, wu, wd, idx, np.where(idx < 0, 0.0, gate).astype(np.float32), cfg.dtype)
+    check_forward(got, ref, cfg.dtype, f"fp32 runs singles={singles}")
+
+
 # the three kinds of items of the grouped GEMMs in one block: one expert above
 # 128 rows (half runs, two M groups), whole runs, and the last items' half runs;
 # 18 tiles of I and 34 of H end inside a run and inside a half run

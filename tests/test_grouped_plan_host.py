@@ -1,7 +1,7 @@
 """The item split and the grid of the grouped GEMMs, enumerated on the host: a
 C++ program over csrc/grouped_plan.hpp, the arithmetic the kernels and their
-launch use, checks that the workgroups of a launch cover every half run of every
-item exactly once, for expert row counts at the edges of the split."""
+launch use, checks that the workgroups of a launch cover every part of every run
+of every item exactly once, for expert row counts at the edges of the split."""
 import os
 import shutil
 import subprocess
@@ -25,28 +25,29 @@ static bool covered(const std::vector<int>& counts, int eb, int nblocks) {
   for (int c : counts) {
     slots += c;
     const ItemSplit sp = split_rows(c, eb);
-    int left = c, multiplied = 0;  // M-tiles: a big item of fp32 multiplies four
+    int left = c, multiplied = 0;  // M-tiles: fp32 items of more than 48 rows multiply four
     if (sp.big < 0 || sp.big > sp.items) return false;
     for (int m = 0; m < sp.items; ++m) {
       const int rows = sp.rows < left ? sp.rows : left;
       if (rows < 1 || rows > item_rows || (m >= sp.big && rows > big_rows)) return false;
       left -= rows;
-      multiplied += m < sp.big ? grouped_item_rows(eb) / 16 : (rows + 15) / 16;
+      multiplied += m < sp.big && rows > 48 ? grouped_item_rows(eb) / 16 : (rows + 15) / 16;
     }
-    if (left != 0 || (eb == 4 && multiplied > (c + 15) / 16 + 1)) return false;
+    if (left != 0 || (eb == 4 && multiplied > (c + 15) / 16)) return false;
     n_items += sp.items;
     n_big += sp.big;
   }
   const int max_items = grouped_max_items(slots, static_cast<int>(counts.size()), item_rows);
   if (n_items > max_items) return false;
-  std::vector<int> seen(static_cast<size_t>(n_items) * 2 * nblocks, 0);
-  const long long grid = grouped_workgroups(slots, max_items, big_rows, nblocks);
+  std::vector<int> seen(static_cast<size_t>(n_items) * 4 * nblocks, 0);  // quarter runs
+  const long long grid = grouped_workgroups(slots, max_items, nblocks, eb);
   for (long long b = 0; b < grid; ++b) {
-    const GroupedShare s = grouped_share(static_cast<int>(b), n_items, n_big, nblocks);
+    const GroupedShare s = grouped_share(static_cast<int>(b), n_items, n_big, nblocks, eb);
     if (s.item >= n_items) continue;
-    if (s.item < 0 || s.run < 0 || s.run >= (s.half ? 2 : 1) * nblocks || (s.item < n_big && !s.half)) return false;
-    for (int h = 0; h < (s.half ? 1 : 2); ++h)
-      ++seen[static_cast<size_t>(s.item) * 2 * nblocks + (s.half ? s.run : 2 * s.run + h)];
+    if (s.item < 0 || s.run < 0 || s.run >= s.parts * nblocks || (s.item < n_big && s.parts == 1)) return false;
+    if (s.parts != 1 && s.parts != 2 && !(s.parts == 4 && eb == 4)) return false;
+    for (int q = 0; q < 4 / s.parts; ++q)
+      ++seen[static_cast<size_t>(s.item) * 4 * nblocks + s.run * (4 / s.parts) + q];
   }
   for (int n : seen)
     if (n != 1) return false;
@@ -62,7 +63,7 @@ static int check(const std::vector<int>& counts, int eb, int nblocks, const char
 
 int main() {
   int bad = 0;
-  const int runs[] = {1, 2, 6, 16, 32, 64, 300};
+  const int runs[] = {1, 2, 6, 16, 32, 64, 128, 129, 300};
   // m experts with `a` rows and s with `b`
   for (int eb : {2, 4}) {
     const std::vector<int> big = eb == 2 ? std::vector<int>{129, 193, 257, 384, 385, 386, 577}
