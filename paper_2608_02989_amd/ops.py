@@ -280,8 +280,9 @@ class VerifyLayer:
         # route(), select() and moe_forward() on the layer's own buffers: every
         # tensor is checked once, as those three check it, and the stream looked up
         # once (a small block's step is bound by this host work: T = 8
-        # 33.6 -> 22.8 us a step)
-        _need(hidden, "hidden", self.dtype, 2)
+        # 33.6 -> 22.1 us a step)
+        dt = self.dtype
+        _need(hidden, "hidden", dt, 2)
         _need(depth, "depth", torch.int32, 1)
         _need(prob, "prob", torch.float32, 1)
         if parent is not None:
@@ -290,38 +291,41 @@ class VerifyLayer:
             _need(resident, "resident", torch.uint8, 1)
         T, H = hidden.shape
         offs_np, offs_ptr, B = _offsets(tree_offsets)  # offs_np: alive until the calls return
-        router, wgu, wd = self.router, self.wgu, self.wd
+        router, wgu, wd, E = self.router, self.wgu, self.wd, self.E
         if not isinstance(router, PackedRouter):
             raise TypeError("route needs the router matrix packed by pack_router_weights")
         if not isinstance(wgu, PackedGateUp):
             raise TypeError("w_gate_up must come from pack_gate_up_weights")
-        _need(wgu.data, "w_gate_up", self.dtype, 1)
-        _need(wd, "w_down", self.dtype, 3)
-        if router.H != H or router.E != self.E or H != self.H:
+        gu = wgu.data
+        for w, name, dim in ((gu, "w_gate_up", 1), (wd, "w_down", 3)):
+            if not (isinstance(w, torch.Tensor) and w.dtype == dt and w.is_cuda and w.is_contiguous()):
+                _need(w, name, dt, dim)
+        if router.H != H or router.E != E or H != self.H:
             raise ValueError(f"router packed for H={router.H}, E={router.E}, hidden has H={H}, "
-                             f"the layer H={self.H}, E={self.E}")
+                             f"the layer H={self.H}, E={E}")
         if wgu.H != H or wd.shape != (wgu.E, H, wgu.I):
             raise ValueError("weights must be gate/up packed from [E, I, H] stacks and down [E, H, I]")
         if T > self.max_tokens or B > self.max_trees:
             raise ValueError(f"layer holds {self.max_tokens} tokens in {self.max_trees} trees, got {T} in {B}")
-        # views, not the buffers themselves: what a caller does to their shape or
-        # autograd state does not reach the layer
-        buf = self.sel_out
-        logits, out = self.logits[:T], self.out[:T]
-        outs = {"eligible": buf["eligible"][:B], "idx": buf["idx"][:T], "gate": buf["gate"][:T],
-                "stats": buf["stats"][:B]}
+        logits, buf, out = self.logits, self.sel_out, self.out
         s, code, hp = _stream_ptr(stream), _dtype_code(hidden), hidden.data_ptr()
-        zp, ip, gp = logits.data_ptr(), outs["idx"].data_ptr(), outs["gate"].data_ptr()
+        zp, ip, gp = logits.data_ptr(), buf["idx"].data_ptr(), buf["gate"].data_ptr()
         h = lib()
-        check(h.acceptmoe_route(hp, code, router.data.data_ptr(), T, H, self.E, zp, s))
-        check(h.acceptmoe_select(zp, _ptr(parent), depth.data_ptr(), prob.data_ptr(), offs_ptr, B, T, self.E, self.k,
+        check(h.acceptmoe_route(hp, code, router.data.data_ptr(), T, H, E, zp, s))
+        check(h.acceptmoe_select(zp, _ptr(parent), depth.data_ptr(), prob.data_ptr(), offs_ptr, B, T, E, self.k,
                                  float(self.beta), int(self.mode), int(self.budget), int(self.removal_cap),
                                  _ptr(resident),
-                                 outs["eligible"].data_ptr(), ip, gp, outs["stats"].data_ptr(),
+                                 buf["eligible"].data_ptr(), ip, gp, buf["stats"].data_ptr(),
                                  self.sel_ws.data_ptr(), self.sel_ws.numel(), s))
-        check(h.acceptmoe_moe_forward(hp, code, wgu.data.data_ptr(), wd.data_ptr(), T, H, wgu.I, wgu.E,
+        check(h.acceptmoe_moe_forward(hp, code, gu.data_ptr(), wd.data_ptr(), T, H, wgu.I, wgu.E,
                                       self.k, ip, gp, out.data_ptr(), self.fwd_ws.data_ptr(), self.fwd_ws.numel(), s))
-        return logits, outs, out
+        # views, not the buffers themselves: what a caller does to their shape or
+        # autograd state does not reach the layer.  Made behind the launches, and at
+        # the full size by detach(), which takes a third of a slice's time.
+        if T == self.max_tokens and B == self.max_trees:
+            return logits.detach(), {key: t.detach() for key, t in buf.items()}, out.detach()
+        return (logits[:T], {"eligible": buf["eligible"][:B], "idx": buf["idx"][:T], "gate": buf["gate"][:T],
+                             "stats": buf["stats"][:B]}, out[:T])
 
 
 def residual_add(hidden: torch.Tensor, y: torch.Tensor, out: torch.Tensor | None = None,
