@@ -54,20 +54,19 @@ struct F32Path {
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
 
-// Weight streams.  Every weight fragment is read once per step, through a
-// buffer load whose cache policy is chosen per pass: the gate/up stream is
-// non-temporal; the down stream uses the default policy where H >= 4096 (two
-// column tiles per workgroup, or the per-slot pass) and is non-temporal
-// otherwise.  (Measured on the wide layer, H = 4096, I = 1536: the column-tile
-// down pass takes 68.6 us with default-policy loads against 75.6 us
-// non-temporal, the per-slot down pass at 512 tokens 375 against 396 us; the
-// gate/up pass is fastest non-temporal, 601 against 612 us for plain global
-// non-temporal loads and 621 us with the default policy.  At H = 2048 the
-// default policy saves 0.8 us of the down pass but lets its weights evict the
-// next layer's router planes from the Infinity Cache: the 48-layer pass ran
-// 5027 against 4941 us per block.)  A weight run is addressed by a
-// wave-uniform base and its length in bytes: a load past the run returns
-// zero instead of reading other memory.
+// Weight streams.  Weights go through buffer loads whose cache policy is chosen
+// per pass.  The column path reads every fragment once per 16 to 64 tokens of an
+// expert: its gate/up stream is non-temporal, its down stream takes the default
+// policy where a workgroup has two column tiles (H >= 4096: 68.6 us against 75.6 us
+// non-temporal, H = 4096, I = 1536) and is non-temporal otherwise (at H = 2048 the
+// default policy saves 0.8 us of the down pass but lets its weights evict the next
+// layer's router planes from the Infinity Cache: the 48-layer pass ran 5027
+// against 4941 us per block).  The grouped GEMMs stream non-temporal in one M group
+// (gate/up 478 against 530 us, 8 trees x 64 nodes, H = 4096, I = 1536) and take the
+// default policy in two, which read the same fragments (229 -> 215 us at 32 x 60
+// nodes, H = 2048, I = 768).  A weight run is addressed by a wave-uniform base and
+// its length in bytes: a load past the run returns zero instead of reading other
+// memory.
 constexpr int kPolicyStream = 2;  // "nt": non-temporal
 constexpr int kPolicyPlain = 0;   // default cache policy
 constexpr int kBufferWord3 = 0x00020000;  // raw (untyped) buffer resource, 32-bit data format

@@ -80,7 +80,7 @@ __global__ void pack_gate_up_kernel(const uint4* __restrict__ gate, const uint4*
 // Exclusive scan of per-expert counts and compaction of the active experts,
 // in index order (one wave, lane = tid < 64).  Returns the number of active
 // experts; off[E] = total dispatched slots.
-__device__ __forceinline__ int scan_experts(const int* cnt, int* off, int* active, int* active_g, int E, int tid) {
+__device__ __forceinline__ int scan_experts(const int* cnt, int* off, int* active, int E, int tid) {
   int base = 0, abase = 0;
   for (int e0 = 0; e0 < E; e0 += kWave) {
     const int e = e0 + tid;
@@ -88,11 +88,7 @@ __device__ __forceinline__ int scan_experts(const int* cnt, int* off, int* activ
     const int incl = wave_incl_scan_i32(c);
     if (e < E) off[e] = base + incl - c;
     const uint64_t am = __ballot(c > 0);
-    if (c > 0) {
-      const int pos = abase + popc64(am & lanes_below(tid));
-      active[pos] = e;
-      if (active_g != nullptr) active_g[pos] = e;
-    }
+    if (c > 0) active[abase + popc64(am & lanes_below(tid))] = e;
     abase += popc64(am);
     base += lane_value(incl, kWave - 1);
   }
@@ -122,7 +118,7 @@ __device__ __forceinline__ void write_down_items(const ForwardParams& p, const i
 
 // Items (expert, first CSR row, rows) of the grouped GEMMs, as split_rows cuts
 // each active expert's rows, and their count (one wave).  The big items, which
-// take longest, come first (their count goes to n_active), each group in
+// take longest, come first (their count goes to n_big), each group in
 // active-expert order.
 __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, const int* cnt, const int* off,
                                                     const int* active, int na, int tid) {
@@ -139,7 +135,7 @@ __device__ __forceinline__ void write_grouped_items(const ForwardParams& p, cons
         p.items[base + incl - n + m - first] = make_int4(e, off[e] + sp.rows * m, min(sp.rows, c - sp.rows * m), 0);
       base += lane_value(incl, kWave - 1);
     }
-    if (big != 0 && tid == 0) *p.n_active = base;
+    if (big != 0 && tid == 0) *p.n_big = base;
   }
   if (tid == 0) *p.n_items = base;
 }
@@ -212,7 +208,7 @@ __global__ __launch_bounds__(kDispatchThreads) void dispatch_kernel(ForwardParam
   }
   __syncthreads();
   if (tid < kWave) {
-    const int na = scan_experts(s_cnt, s_off, s_active, nullptr, E, tid);
+    const int na = scan_experts(s_cnt, s_off, s_active, E, tid);
     if (tid == 0) s_nact = na;
   }
   __syncthreads();
@@ -290,7 +286,7 @@ __device__ __forceinline__ void self_dispatch(const ForwardParams& p, SelfDispat
   }
   __syncthreads();
   if (tid < kWave) {
-    const int na = scan_experts(sd.cnt, sd.off, sd.active, nullptr, E, tid);
+    const int na = scan_experts(sd.cnt, sd.off, sd.active, E, tid);
     if (tid == 0) sd.nact = na;
   }
   __syncthreads();
@@ -335,16 +331,11 @@ __device__ __forceinline__ int nth_set_bit(const uint32_t* mask, int words, int 
   return 32 * w + __builtin_ctz(m);
 }
 
-// CSR, active list and down items to the workspace
+// CSR rows and down items to the workspace
 __device__ __forceinline__ void publish_dispatch(const ForwardParams& p, const SelfDispatch& sd, int tid) {
-  const int E = p.E;
-  for (int e = tid; e <= E; e += 256) {
-    p.off[e] = sd.off[e];
-    if (e < E) p.cnt[e] = sd.cnt[e];
-  }
-  for (int i = tid; i < sd.nact; i += 256) p.active[i] = sd.active[i];
-  for (int i = tid; i < sd.off[E]; i += 256) p.ent_slot[i] = sd.ent[i];
-  if (tid == 0) *p.n_active = sd.nact;
+  const int n_rows = sd.off[p.E];
+  for (int i = tid; i < n_rows; i += 256) p.ent_slot[i] = sd.ent[i];
+  if (tid == 0) *p.n_rows = n_rows;
   if (tid < kWave) write_down_items(p, sd.cnt, sd.off, sd.active, sd.nact, tid);
 }
 
@@ -709,7 +700,7 @@ __global__ __launch_bounds__(kColLanes / NB * kWave) void down_col_kernel(Forwar
   const int L = (KC / ksplit) / kU;  // pipeline stages per item
   const int rowq = p.I * P::kElemBytes / 16;
   const int n_items = *p.n_items;
-  const int n_rows = p.off[p.E];
+  const int n_rows = *p.n_rows;
   // this wave's first item straight from the workspace, so the first stage's
   // loads are in flight while the lists are staged in LDS
   int4 first = make_int4(0, 0, 1, 0);
@@ -1049,13 +1040,13 @@ int max_grouped_items(int T, int E, int k, int is_bf16) {
   return grouped_max_items(T * k, E, grouped_item_rows(is_bf16 ? 2 : 4));
 }
 
-// workspace: [cnt E | off E+1 | active E | n_active | n_items] ints, CSR slot
+// workspace: [n_items | n_big | n_rows] ints, CSR slot
 // ids, activations, then the items of the grouped GEMMs and the per-slot
 // output rows (grouped path) or the down items (column-tile path)
 size_t forward_workspace_bytes(int T, int H, int I, int E, int k, int is_bf16) {
   const size_t slots = static_cast<size_t>(T) * k;
   const size_t eb = is_bf16 ? 2 : 4;
-  const size_t head = align256(sizeof(int32_t) * (3 * static_cast<size_t>(E) + 3)) +
+  const size_t head = align256(sizeof(int32_t) * 3) +
                       align256(sizeof(int32_t) * slots) + align256(slots * I * eb);
   if (use_col_path(T, H, I, E, k, is_bf16)) {
     const size_t items = (slots + 15) / 16 + (static_cast<size_t>(E) < slots ? E : slots);
@@ -1070,12 +1061,10 @@ void forward_carve(void* ws, ForwardParams& p) {
   const size_t slots = static_cast<size_t>(p.T) * p.k;
   const size_t eb = p.is_bf16 ? 2 : 4;
   int32_t* ints = reinterpret_cast<int32_t*>(c);
-  p.cnt = ints;
-  p.off = ints + p.E;
-  p.active = ints + 2 * p.E + 1;
-  p.n_active = ints + 3 * p.E + 1;
-  p.n_items = ints + 3 * p.E + 2;
-  c += align256(sizeof(int32_t) * (3 * static_cast<size_t>(p.E) + 3));
+  p.n_items = ints;
+  p.n_big = ints + 1;
+  p.n_rows = ints + 2;
+  c += align256(sizeof(int32_t) * 3);
   p.ent_slot = reinterpret_cast<int32_t*>(c);
   c += align256(sizeof(int32_t) * slots);
   p.act = c;

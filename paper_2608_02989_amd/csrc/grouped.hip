@@ -2,12 +2,13 @@
 // gate-scaled slot rows.
 //
 // A workgroup of 4 waves takes one item (expert, up to 192 of its dispatched
-// rows) and one run of output tiles.  Each wave streams the weights of its own
-// tiles straight into registers (4 fragments per K chunk: a gate/up tile pair,
-// or four 16-column tiles of the down projection); the item's rows are staged
-// in LDS, once for the four waves, and every fragment read from there meets
-// four weight fragments.  The rows are fetched once per 128 rows of I (256
-// columns of H).
+// rows, fp32: 64) and one run of output tiles, or half or a quarter of one (see
+// grouped_kernel).  Each wave streams the weights of its own tiles straight into
+// registers (4 fragments per K chunk: a gate/up tile pair, or four 16-column tiles
+// of the down projection; 2 in smaller runs); the item's rows are staged in LDS,
+// once for the four waves, and every fragment read from there meets those weight
+// fragments.  The rows are fetched once per 128 rows of I (256 columns of H), by
+// half and quarter runs once per 64 and 32 (128 and 64).
 //
 // What bounds it: the weight stream at 15 to 60 tokens per expert (8 trees x
 // 64 nodes, H = 4096, I = 1536: gate/up streams 3.0 GB in 480 us = 6.3 TB/s,
@@ -30,14 +31,15 @@ namespace amoe {
 namespace {
 
 constexpr int kGrpStage = 2;  // K chunks per LDS stage (128 bytes of each row)
-constexpr int kGrpFrags = 4;  // most weight fragments per wave and K chunk (2 in a half run)
 
 enum class Grouped { GateUp, Down };
 
 // M-tiles per wave: the accumulators of 8 M-tiles x 4 fragments are half of
 // the registers two workgroups per CU leave a wave.  With two M groups each
 // thread also holds twice the rows in flight: 6.  The fp32 path keeps a second
-// accumulator set (below): 3.
+// accumulator set (below): 2 (3 x 4 fragments spill 64 registers).  One bf16
+// kernel holds all M-tile counts at the 256 registers; the compiler spills 6 of
+// them in gate/up and 2 in down.
 template <class P>
 constexpr int kGrpTileM = grouped_tile_m(P::kElemBytes);
 template <class P>
@@ -165,10 +167,14 @@ struct GroupedRows {  // an item's slots and their gates
   float gate[kGrpMaxRows<P>];
 };
 
-// 16-byte pieces of LDS: two stages of an item's rows (M-tiles rounded up to
-// an even number, see grouped_product)
+// 16-byte pieces of LDS: two stages of an item's rows (M-tiles rounded up to an
+// even number, see grouped_product), or four waves' M-tiles of 4 x 16 floats and a
+// padding piece per row on their way out, whichever is more.
 template <class P>
-constexpr int kGrpLds = 2 * kGrpStage * (2 * kGrpTileM2<P> + 1) / 2 * 2 * kWave;
+constexpr int kGrpStaging = 2 * kGrpStage * 2 * ((2 * kGrpTileM2<P> + 1) / 2) * kWave;
+constexpr int kGrpOut = 4 * 16 * 17;
+template <class P>
+constexpr int kGrpLds = kGrpStaging<P> > kGrpOut ? kGrpStaging<P> : kGrpOut;
 
 // MT M-tiles per wave, FR weight fragments.  MG = 2: the item has 2 MT M-tiles
 // and the four waves are two M groups over half as many output tiles.  MG = 2
@@ -358,11 +364,12 @@ __device__ __forceinline__ void grouped_quarter(const ForwardParams& p, int e, i
 // 8 x 64 (H = 4096) even.
 template <class P, Grouped F>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void grouped_kernel(ForwardParams p,
-                                                                                              int nblocks) {
+                                                                                              int nblocks,
+                                                                                              int n_split) {
   __shared__ uint4 lds[kGrpLds<P>];
   __shared__ GroupedRows<P> gr;
-  const int n_items = *p.n_items, n_big = *p.n_active;
-  const GroupedShare sh = grouped_share(blockIdx.x, n_items, n_big, nblocks, P::kElemBytes);
+  const int n_items = *p.n_items, n_big = *p.n_big;
+  const GroupedShare sh = grouped_share(blockIdx.x, n_items, n_big, n_split, nblocks, P::kElemBytes);
   if (sh.item >= n_items) return;
   const int4 d = p.items[sh.item];
   const int run = __builtin_amdgcn_readfirstlane(sh.run);  // without this the gate/up kernel spills 65 registers, not 6
@@ -395,7 +402,7 @@ hipError_t launch_grouped_pass(const ForwardParams& p, int max_items, int nblock
   const long long grid = grouped_workgroups(p.T * p.k, max_items, nblocks, P::kElemBytes);
   // far beyond what the slot rows of one device's memory allow
   if (grid > 0x7fffffffll) return hipErrorInvalidValue;
-  grouped_kernel<P, F><<<static_cast<unsigned>(grid), 256, 0, stream>>>(p, nblocks);
+  grouped_kernel<P, F><<<static_cast<unsigned>(grid), 256, 0, stream>>>(p, nblocks, grouped_split_items(nblocks));
   return hipGetLastError();
 }
 

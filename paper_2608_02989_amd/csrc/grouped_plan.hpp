@@ -64,31 +64,25 @@ constexpr bool grouped_quarters(int n_items, int nblocks, int elem_bytes) {
 struct GroupedShare {
   int item, run, parts;
 };
-constexpr GroupedShare grouped_share(int block, int n_items, int n_big, int nblocks, int elem_bytes) {
+constexpr GroupedShare grouped_share(int block, int n_items, int n_big, int n_split, int nblocks, int elem_bytes) {
   const int xcd = block % 8;
-  if (grouped_quarters(n_items, nblocks, elem_bytes)) {
-    const int slot = block / 8, item = slot / (4 * nblocks);
-    return {item * 8 + xcd, slot - item * 4 * nblocks, 4};
-  }
-  const int n_split = grouped_split_items(nblocks);
   const int n_whole = n_big > n_items - n_split ? n_big : n_items - n_split;  // items [n_big, n_whole) take whole runs
   const int big = (n_big + 7 - xcd) / 8, whole = (n_whole + 7 - xcd) / 8;      // of the first n items on this XCD
-  int slot = block / 8, item = 0, parts = 2;
-  if (slot < 2 * nblocks * big) {
-    item = slot / (2 * nblocks);
-    slot -= item * 2 * nblocks;
-  } else if (slot -= 2 * nblocks * big; slot < nblocks * (whole - big)) {
+  int slot = block / 8, first = 0, parts = 2;  // item `first` of the XCD starts at slot 0
+  if (grouped_quarters(n_items, nblocks, elem_bytes)) {
+    parts = 4;
+  } else if (slot >= 2 * nblocks * big) {
+    slot -= 2 * nblocks * big;
+    first = big;
     parts = 1;
-    item = slot / nblocks;
-    slot -= item * nblocks;
-    item += big;
-  } else {
-    slot -= nblocks * (whole - big);
-    item = slot / (2 * nblocks);
-    slot -= item * 2 * nblocks;
-    item += whole;
+    if (slot >= nblocks * (whole - big)) {
+      slot -= nblocks * (whole - big);
+      first = whole;
+      parts = 2;
+    }
   }
-  return {item * 8 + xcd, slot, parts};
+  const int item = slot / (parts * nblocks);  // one division for all: a branch each cost every workgroup three
+  return {(first + item) * 8 + xcd, slot - item * parts * nblocks, parts};
 }
 
 // Workgroups that cover every item's nblocks runs for any routing of `slots`

@@ -76,15 +76,13 @@ struct ForwardParams {
   const float* topk_gate;
   float* out;
   // workspace
-  int32_t* cnt;       // [E]
-  int32_t* off;       // [E + 1]
-  int32_t* active;    // [E]
-  int32_t* n_active;  // [1] routed experts (column path) or big items (grouped path)
   int32_t* ent_slot;  // [T * k] slot ids grouped by expert, token order
   void* act;          // [T * k, I] bf16 or fp32
   float* ys;          // [T * k, H] gate-weighted expert outputs (grouped path only)
   int4* items;        // work items (e, first CSR row, rows): column-tile down pass or grouped GEMMs
   int32_t* n_items;   // [1]
+  int32_t* n_big;     // [1] of them big items, which come first (grouped path)
+  int32_t* n_rows;    // [1] dispatched slots (column path)
   int T, H, I, E, k, is_bf16;
   int zero_out;       // gate/up pass clears out (the down pass then adds two halves into it)
   int item_rows;      // most rows of a column-tile down item (16 per M-tile)

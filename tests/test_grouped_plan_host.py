@@ -42,7 +42,7 @@ static bool covered(const std::vector<int>& counts, int eb, int nblocks) {
   std::vector<int> seen(static_cast<size_t>(n_items) * 4 * nblocks, 0);  // quarter runs
   const long long grid = grouped_workgroups(slots, max_items, nblocks, eb);
   for (long long b = 0; b < grid; ++b) {
-    const GroupedShare s = grouped_share(static_cast<int>(b), n_items, n_big, nblocks, eb);
+    const GroupedShare s = grouped_share(static_cast<int>(b), n_items, n_big, grouped_split_items(nblocks), nblocks, eb);
     if (s.item >= n_items) continue;
     if (s.item < 0 || s.run < 0 || s.run >= s.parts * nblocks || (s.item < n_big && s.parts == 1)) return false;
     if (s.parts != 1 && s.parts != 2 && !(s.parts == 4 && eb == 4)) return false;
