@@ -342,17 +342,37 @@ __device__ __forceinline__ void publish_dispatch(const ForwardParams& p, const S
 // k-steps per pipeline stage of the gate/up stream; two stages are kept in flight
 constexpr int kGateUpKU = 1;
 
-// acc[nb][mt] += sum over the K chunks c_i = c_first + i * c_step, 0 <= i < n,
+// sum[nb][mt] += sum over the K chunks c_i = c_first + i * c_step, 0 <= i < n,
 // of x[mt] (A, tokens) times w[nb] (B, weight rows).  w[nb] is the wave-uniform
 // start of a weight run of wbytes bytes, in which chunk c's fragment sits at
 // piece c * wstride + lane; x[mt] points at this lane's 16-byte piece of chunk
 // 0 and chunk c sits c * 4 pieces further.  Loads run two stages ahead of the
 // MFMAs and carry no branches, so the only waits are the in-order vmcnt
-// waits on the stage being consumed.
-template <class P, int MT, int NB, int kPolicy>
+// waits on the stage being consumed.  kSums: sums of 16 of the chunks, then the
+// sums (see col_sums); the branch for it sits behind a stage's MFMAs.
+template <class P, int MT, int NB, int kPolicy, bool kSums>
 __device__ __forceinline__ void stream_tiles(const uint4* const (&w)[NB], int wbytes, const uint4* const (&x)[MT],
-                                             int c_first, int c_step, int n, int wstride, floatx4 (&acc)[NB][MT]) {
+                                             int c_first, int c_step, int n, int wstride, floatx4 (&sum)[NB][MT]) {
   constexpr int kU = kGateUpKU;
+  floatx4 part[NB][MT];
+  floatx4 (&acc)[NB][MT] = kSums ? part : sum;
+  if (kSums) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) part[nb][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto flush = [&]() {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          sum[nb][mt][q] += part[nb][mt][q];
+          part[nb][mt][q] = 0.f;
+        }
+  };
   const int lane = lane_id();
   uint4 wb0[kU][NB], wb1[kU][NB], xb0[kU][MT], xb1[kU][MT];
   auto load0 = [&](int i) {
@@ -409,6 +429,7 @@ __device__ __forceinline__ void stream_tiles(const uint4* const (&w)[NB], int wb
       load0((st + 2) * kU);
       __builtin_amdgcn_sched_barrier(0);
       comp1();
+      if (kSums && st % 16 == 14) flush();
     }
     if (st + 1 < nst) {
       load1((st + 1) * kU);
@@ -431,6 +452,7 @@ __device__ __forceinline__ void stream_tiles(const uint4* const (&w)[NB], int wb
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) acc[nb][mt] = P::mma(xt[mt], wt[nb], acc[nb][mt]);
   }
+  if (kSums) flush();
 }
 
 // ---------------------------------------------------------------------------
@@ -450,7 +472,7 @@ constexpr int kTilesPerWG = 2;     // one tile pair
 constexpr int kGateUpFrags = 4;    // weight fragments per K chunk
 
 // ent_e: the n_e slot ids of expert e in node order; o_e: its first row in act
-template <class P, int MT>
+template <class P, int MT, bool kSums>
 __device__ __forceinline__ void gate_up_pass(const ForwardParams& p, const int32_t* ent_e, int e, int tile0, int n_e,
                                              int o_e, int m0, floatx4 (*red)[kWave][4]) {
   constexpr int NB = kGateUpFrags, KS = kGateUpKS;
@@ -485,7 +507,7 @@ __device__ __forceinline__ void gate_up_pass(const ForwardParams& p, const int32
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[nb][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  stream_tiles<P, MT, NB, kPolicyStream>(w, wbytes, x, wave, KS, (KC - wave + KS - 1) / KS, wstride, acc);
+  stream_tiles<P, MT, NB, kPolicyStream, kSums>(w, wbytes, x, wave, KS, (KC - wave + KS - 1) / KS, wstride, acc);
 
   // fixed-order sum of the KS partial tiles, four fragments per LDS round
 #pragma unroll
@@ -555,7 +577,7 @@ constexpr int kSelfGridMult = 3;
 
 // Occupancy floor: three workgroups per CU for up to two M-tiles, two for
 // more (the register budget the streaming loop is tuned to).
-template <class P, int MTMAX, int KMAX>
+template <class P, int MTMAX, int KMAX, bool kSums>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MTMAX <= 2 ? 3 : 2))) void gate_up_kernel(
     ForwardParams p) {
   __shared__ floatx4 red[kGateUpKS][kWave][4];
@@ -573,10 +595,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MTMAX <= 2 
   auto run_expert = [&](int tile0, int e, int n_e, int o_e, const int32_t* ent_e) {
     for (int m0 = 0; m0 < n_e; m0 += 16 * MTMAX) {
       const int mt = min(MTMAX, (n_e - m0 + 15) / 16);
-      if (mt == 1) gate_up_pass<P, 1>(p, ent_e, e, tile0, n_e, o_e, m0, red);
-      else if (MTMAX >= 2 && mt == 2) gate_up_pass<P, (MTMAX >= 2 ? 2 : 1)>(p, ent_e, e, tile0, n_e, o_e, m0, red);
-      else if (MTMAX >= 3 && mt == 3) gate_up_pass<P, (MTMAX >= 3 ? 3 : 1)>(p, ent_e, e, tile0, n_e, o_e, m0, red);
-      else gate_up_pass<P, MTMAX>(p, ent_e, e, tile0, n_e, o_e, m0, red);
+      if (mt == 1) gate_up_pass<P, 1, kSums>(p, ent_e, e, tile0, n_e, o_e, m0, red);
+      else if (MTMAX >= 2 && mt == 2) gate_up_pass<P, (MTMAX >= 2 ? 2 : 1), kSums>(p, ent_e, e, tile0, n_e, o_e, m0, red);
+      else if (MTMAX >= 3 && mt == 3) gate_up_pass<P, (MTMAX >= 3 ? 3 : 1), kSums>(p, ent_e, e, tile0, n_e, o_e, m0, red);
+      else gate_up_pass<P, MTMAX, kSums>(p, ent_e, e, tile0, n_e, o_e, m0, red);
     }
   };
   const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
@@ -682,7 +704,7 @@ struct ColShared {
   int4 items[kColMaxItems];
 };
 
-template <class P, int kU, int NB, int MTI>
+template <class P, int kU, int NB, int MTI, bool kSums>
 __global__ __launch_bounds__(kColLanes / NB * kWave) void down_col_kernel(ForwardParams p, int ksplit) {
   constexpr int kWaves = kColLanes / NB;
   constexpr int kThreads = kWaves * kWave;
@@ -755,11 +777,12 @@ __global__ __launch_bounds__(kColLanes / NB * kWave) void down_col_kernel(Forwar
       for (int mt = 0; mt < MTI; ++mt) xv[u][mt] = xp[mt][u * 4];
     }
   };
-  floatx4 acc[NB][MTI];
+  constexpr int kRun = 16 / kU > 0 ? 16 / kU : 1;  // stages of a sum
+  floatx4 acc[NB][MTI], sum[NB][MTI];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int mt = 0; mt < MTI; ++mt) acc[nb][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MTI; ++mt) acc[nb][mt] = sum[nb][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
   auto compute = [&](uint4 (&wv)[kU][NB], uint4 (&xv)[kU][MTI], Cursor& c) {
 #pragma unroll
     for (int u = 0; u < kU; ++u)
@@ -767,6 +790,17 @@ __global__ __launch_bounds__(kColLanes / NB * kWave) void down_col_kernel(Forwar
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int mt = 0; mt < MTI; ++mt) acc[nb][mt] = P::mma(xv[u][mt], wv[u][nb], acc[nb][mt]);
+    if (kSums && (c.q % kRun == kRun - 1 || c.q == L - 1)) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mt = 0; mt < MTI; ++mt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            sum[nb][mt][i] += acc[nb][mt][i];
+            acc[nb][mt][i] = 0.f;
+          }
+    }
     if (c.q == L - 1) {
       // item done: out_w[t] += gate * row, rows 16 mt + 4g .. +3 of the item, column r of each tile
 #pragma unroll
@@ -779,14 +813,14 @@ __global__ __launch_bounds__(kColLanes / NB * kWave) void down_col_kernel(Forwar
             float* dst = accw + sh.tok[row] * kCols + r;
             const float gt = sh.gw[row];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) dst[16 * nb] += gt * acc[nb][mt][i];
+            for (int nb = 0; nb < NB; ++nb) dst[16 * nb] += gt * (kSums ? sum : acc)[nb][mt][i];
           }
         }
       }
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int mt = 0; mt < MTI; ++mt) acc[nb][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < MTI; ++mt) acc[nb][mt] = sum[nb][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
     advance(c);
   };
@@ -880,19 +914,19 @@ int resident_workgroups() {
 // Rows of 9 to 16 slots have an instantiation of their own: the search for
 // repeated experts grows with the square of the row (512 experts, top-10,
 // T = 64: 9.7 us before the first weight with rows of 32, pass 93.5 -> 82.7 us).
-template <class P, int MTMAX>
+template <class P, int MTMAX, bool kSums = false>
 hipError_t launch_gate_up(const ForwardParams& p, int cap, hipStream_t stream) {
   const int items = cap * ((p.I / 16 + kTilesPerWG - 1) / kTilesPerWG);
   if (p.k <= 8) {
-    constexpr auto kern = &gate_up_kernel<P, MTMAX, 8>;
+    constexpr auto kern = &gate_up_kernel<P, MTMAX, 8, kSums>;
     const int res = (p.H >= 4096 ? kSelfGridMult : 1) * resident_workgroups<kern>();
     kern<<<dim3((items < res ? items : res) + 1), 256, 0, stream>>>(p);
   } else if (p.k <= 16) {
-    constexpr auto kern = &gate_up_kernel<P, MTMAX, 16>;
+    constexpr auto kern = &gate_up_kernel<P, MTMAX, 16, kSums>;
     const int res = (p.H >= 4096 ? kSelfGridMult : 1) * resident_workgroups<kern>();
     kern<<<dim3((items < res ? items : res) + 1), 256, 0, stream>>>(p);
   } else {
-    constexpr auto kern = &gate_up_kernel<P, MTMAX, kMaxTopK>;
+    constexpr auto kern = &gate_up_kernel<P, MTMAX, kMaxTopK, kSums>;
     const int res = (p.H >= 4096 ? kSelfGridMult : 1) * resident_workgroups<kern>();
     kern<<<dim3((items < res ? items : res) + 1), 256, 0, stream>>>(p);
   }
@@ -977,32 +1011,44 @@ bool use_col_path(int T, int H, int I, int E, int k, int is_bf16) {
   return slots * I <= (c.ku == 1 ? 640 : 1920) * down_wgs;
 }
 
-template <class P, int NB, int MTI>
+// fp32 blocks of more than 192 tokens on the column path add sums of 16 chunks, as
+// the grouped path does for the blocks beside them: error against 64 bits 4.9e-7,
+// 5.1e-7 grouped, 6.9e-7 with one running sum (200 tokens, 128 experts, top-1,
+// H = 2048, I = 768).  The second accumulators leave room for three M-tiles in
+// gate/up.  Smaller blocks keep one running sum: a few tokens are up to 4 % slower
+// with sums.
+constexpr int kColSumsT = 192;
+bool col_sums(const ForwardParams& p) { return !p.is_bf16 && p.T > kColSumsT; }
+
+template <class P, int NB, int MTI, bool kSums = false>
 hipError_t launch_down_col_nb(const ForwardParams& p, const ColShape& c, hipStream_t stream) {
   const dim3 grid((p.H / 16 / NB) * c.ksplit);
   constexpr int threads = kColLanes / NB * kWave;
   if constexpr (NB == 1) {  // deeper stages only with one column tile (col_shape)
     if constexpr (MTI == 1) {
       if (c.ku == 12 || c.ku == 8) {
-        if (c.ku == 12) down_col_kernel<P, 12, NB, MTI><<<grid, threads, 0, stream>>>(p, c.ksplit);
-        else down_col_kernel<P, 8, NB, MTI><<<grid, threads, 0, stream>>>(p, c.ksplit);
+        if (c.ku == 12) down_col_kernel<P, 12, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
+        else down_col_kernel<P, 8, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
         return hipGetLastError();
       }
     }
     if (c.ku == 6) {
-      down_col_kernel<P, 6, NB, MTI><<<grid, threads, 0, stream>>>(p, c.ksplit);
+      down_col_kernel<P, 6, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
       return hipGetLastError();
     }
   }
-  if (c.ku == 4) down_col_kernel<P, 4, NB, MTI><<<grid, threads, 0, stream>>>(p, c.ksplit);
-  else if (c.ku == 3) down_col_kernel<P, 3, NB, MTI><<<grid, threads, 0, stream>>>(p, c.ksplit);
-  else if (c.ku == 2) down_col_kernel<P, 2, NB, MTI><<<grid, threads, 0, stream>>>(p, c.ksplit);
-  else down_col_kernel<P, 1, NB, MTI><<<grid, threads, 0, stream>>>(p, c.ksplit);
+  if (c.ku == 4) down_col_kernel<P, 4, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
+  else if (c.ku == 3) down_col_kernel<P, 3, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
+  else if (c.ku == 2) down_col_kernel<P, 2, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
+  else down_col_kernel<P, 1, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
   return hipGetLastError();
 }
 
 template <class P>
 hipError_t launch_down_col(const ForwardParams& p, const ColShape& c, hipStream_t stream) {
+  if constexpr (P::kElemBytes == 4)
+    if (col_sums(p))  // then mti = nb
+      return c.nb == 2 ? launch_down_col_nb<P, 2, 2, true>(p, c, stream) : launch_down_col_nb<P, 1, 1, true>(p, c, stream);
   if (c.mti == 2)
     return c.nb == 2 ? launch_down_col_nb<P, 2, 2>(p, c, stream) : launch_down_col_nb<P, 1, 2>(p, c, stream);
   return c.nb == 2 ? launch_down_col_nb<P, 2, 1>(p, c, stream) : launch_down_col_nb<P, 1, 1>(p, c, stream);
@@ -1091,7 +1137,8 @@ hipError_t launch_forward(ForwardParams p, hipStream_t stream) {
     if (p.is_bf16)
       err = small_t ? launch_gate_up<Bf16Path, 2>(p, cap, stream) : launch_gate_up<Bf16Path, 4>(p, cap, stream);
     else
-      err = small_t ? launch_gate_up<F32Path, 2>(p, cap, stream) : launch_gate_up<F32Path, 4>(p, cap, stream);
+      err = small_t ? launch_gate_up<F32Path, 2>(p, cap, stream)
+            : col_sums(p) ? launch_gate_up<F32Path, 3, true>(p, cap, stream) : launch_gate_up<F32Path, 4>(p, cap, stream);
     if (err != hipSuccess) return err;
     return p.is_bf16 ? launch_down_col<Bf16Path>(p, cs, stream) : launch_down_col<F32Path>(p, cs, stream);
   }

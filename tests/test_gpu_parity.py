@@ -38,6 +38,10 @@ def to_dev_hidden(cfg, arr):
     return torch.from_numpy(np.ascontiguousarray(arr, np.float32)).to(DEV)
 
 
+def normwise_l2(got, ref):
+    return float(np.linalg.norm(np.asarray(got, np.float64) - ref) / np.linalg.norm(ref))
+
+
 def i32(a):
     return torch.from_numpy(np.ascontiguousarray(a, np.int32)).to(DEV)
 
@@ -567,7 +571,9 @@ def test_forward_parity_grouped_runs(gpu, dtype, H, I):
     ("bf16", 116, 1024, 352, 24, 1, False), ("bf16", 117, 1024, 352, 24, 1, True),
     ("bf16", 256, 128, 256, 16, 8, True), ("bf16", 256, 128, 224, 16, 8, False), ("bf16", 70, 128, 256, 40, 32, True),
     ("f32", 192, 256, 256, 20, 3, False), ("f32", 193, 256, 256, 20, 3, True), ("f32", 240, 256, 256, 20, 1, False),
-    ("f32", 241, 256, 256, 20, 1, True), ("f32", 193, 256, 352, 20, 1, True), ("f32", 256, 256, 256, 20, 8, True)])
+    ("f32", 241, 256, 256, 20, 1, True), ("f32", 193, 256, 352, 20, 1, True), ("f32", 256, 256, 256, 20, 8, True),
+    # two column tiles; experts of 60 to 70 rows, two passes of three M-tiles and fewer
+    ("f32", 193, 4096, 256, 20, 1, False), ("f32", 200, 256, 256, 3, 1, False), ("f32", 256, 128, 48, 16, 8, False)])
 def test_forward_parity_path_edges(gpu, dtype, T, H, I, E, k, grouped):
     cfg = W.LayerConfig("edges", 1400 + T + I + E, dtype, T=T, B=1, H=H, E=E, k=k, I=I, depth_max=6,
                         commit_rule="depth_sibling", hidden_std=1.0)
@@ -581,6 +587,25 @@ def test_forward_parity_path_edges(gpu, dtype, T, H, I, E, k, grouped):
     got, h64, (wg, wu, wd) = forward_case(cfg, idx, gate, h32)
     ref = O.moe_forward_grouped(h64, wg, wu, wd, idx, gate, cfg.dtype)
     check_forward(got, ref, cfg.dtype, f"edges {dtype} T={T} H={H} I={I} E={E} k={k}")
+
+
+# fp32 blocks just above the line between the paths keep the grouped path's error
+# on the column path: both add sums of 16 chunks (4.9e-7 to 5.5e-7 measured here and
+# on the grouped path); one running sum over all of K gives 6.9e-7 to 1.1e-6
+@pytest.mark.parametrize("E,k,H,I", [(128, 1, 2048, 768), (64, 2, 4064, 320), (32, 1, 3424, 1952)])
+def test_forward_fp32_column_error(gpu, E, k, H, I):
+    T = 200
+    assert L.lib().acceptmoe_moe_forward_workspace_size(T, H, I, E, k, L.F32) < T * k * (I * 4 + H * 4)
+    cfg = W.LayerConfig("colerr", 1600 + I, "f32", T=T, B=1, H=H, E=E, k=k, I=I, depth_max=6,
+                        commit_rule="depth_sibling", hidden_std=1.0)
+    rng = np.random.default_rng(I)
+    h32 = rng.standard_normal((T, H)).astype(np.float32)
+    idx = np.stack([rng.permutation(E)[:k] for _ in range(T)]).astype(np.int32)
+    gate = rng.random((T, k)).astype(np.float32)
+    got, h64, (wg, wu, wd) = forward_case(cfg, idx, gate, h32)
+    err = normwise_l2(got, O.moe_forward_grouped(h64, wg, wu, wd, idx, gate, cfg.dtype))
+    say(f"forward fp32 column error E={E} k={k} H={H} I={I}: {err:.3e}")
+    assert err <= 6.2e-7, err
 
 
 # one layer, one workspace: blocks of the grouped path, then of the column path,
