@@ -973,7 +973,8 @@ void select_carve(void* ws, int T, int E, int k, SelectParams& p) {
 // E = 128, 1 node 7.6 / 10.2, 6 nodes 9.6 / 12.6, 16 nodes 11.4 / 12.8, 16
 // trees of 16 11.8 / 13.9; two nodes per wave 32 nodes 18.2 / 13.5.
 // E = 512, whose rows take four times the work: 8 nodes 14.8 / 18.8 (kernels
-// alone), 16 nodes 20.0 / 19.0.  The MoE-Spec mode needs whole softmax rows in
+// alone), 16 nodes 20.0 / 19.0.  E = 256: 16 nodes, top-8 15.7 / 17.4, top-32 20.9 /
+// 21.6; 200 trees of 16, top-8 16.6 / 22.3.  The MoE-Spec mode needs whole softmax rows in
 // the workspace and stays with three.
 bool fused_select(const SelectParams& p, const TreeOffsets& offs) {
   const int most = p.E <= 256 ? kFusedNodes : kFusedNodes / 2;
