@@ -947,10 +947,6 @@ struct ColShape {
   int ksplit, ku, nb, mti;
 };
 
-#ifndef AMOE_COL_MTI
-#define AMOE_COL_MTI 0
-#endif
-
 // M-tiles per down item: two (items of up to 32 tokens) for blocks of more
 // than 32 tokens when the workgroup owns two column tiles, whose stages are
 // capped at 4 k-steps either way (H = 4096, T = 64: forward 188.7 -> 182.9 us);
@@ -962,10 +958,10 @@ ColShape col_shape(int T, int H, int I, int is_bf16) {
   const int ntiles = H / 16;
   ColShape c;
   c.nb = (ntiles >= 256 && ntiles % 2 == 0) ? 2 : 1;
-  c.mti = AMOE_COL_MTI ? AMOE_COL_MTI : (T > 32 && c.nb == 2 ? 2 : 1);
+  c.mti = T > 32 && c.nb == 2 ? 2 : 1;
   c.ksplit = (ntiles / c.nb <= 128 && KC % 2 == 0) ? 2 : 1;
   const int len = KC / c.ksplit;
-  const int ku_max = c.nb == 1 ? (c.mti == 1 ? 12 : 6) : 4;
+  const int ku_max = c.nb == 1 ? 12 : 4;
   c.ku = 1;
   for (const int u : {12, 8, 6, 4, 3, 2}) {
     if (len % u == 0 && u <= ku_max) {
@@ -1025,15 +1021,10 @@ hipError_t launch_down_col_nb(const ForwardParams& p, const ColShape& c, hipStre
   const dim3 grid((p.H / 16 / NB) * c.ksplit);
   constexpr int threads = kColLanes / NB * kWave;
   if constexpr (NB == 1) {  // deeper stages only with one column tile (col_shape)
-    if constexpr (MTI == 1) {
-      if (c.ku == 12 || c.ku == 8) {
-        if (c.ku == 12) down_col_kernel<P, 12, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
-        else down_col_kernel<P, 8, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
-        return hipGetLastError();
-      }
-    }
-    if (c.ku == 6) {
-      down_col_kernel<P, 6, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
+    if (c.ku > 4) {
+      if (c.ku == 12) down_col_kernel<P, 12, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
+      else if (c.ku == 8) down_col_kernel<P, 8, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
+      else down_col_kernel<P, 6, NB, MTI, kSums><<<grid, threads, 0, stream>>>(p, c.ksplit);
       return hipGetLastError();
     }
   }
@@ -1047,11 +1038,10 @@ hipError_t launch_down_col_nb(const ForwardParams& p, const ColShape& c, hipStre
 template <class P>
 hipError_t launch_down_col(const ForwardParams& p, const ColShape& c, hipStream_t stream) {
   if constexpr (P::kElemBytes == 4)
-    if (col_sums(p))  // then mti = nb
+    if (col_sums(p))  // more than 32 tokens, so mti = nb
       return c.nb == 2 ? launch_down_col_nb<P, 2, 2, true>(p, c, stream) : launch_down_col_nb<P, 1, 1, true>(p, c, stream);
-  if (c.mti == 2)
-    return c.nb == 2 ? launch_down_col_nb<P, 2, 2>(p, c, stream) : launch_down_col_nb<P, 1, 2>(p, c, stream);
-  return c.nb == 2 ? launch_down_col_nb<P, 2, 1>(p, c, stream) : launch_down_col_nb<P, 1, 1>(p, c, stream);
+  if (c.nb == 1) return launch_down_col_nb<P, 1, 1>(p, c, stream);
+  return c.mti == 2 ? launch_down_col_nb<P, 2, 2>(p, c, stream) : launch_down_col_nb<P, 2, 1>(p, c, stream);
 }
 
 }  // namespace

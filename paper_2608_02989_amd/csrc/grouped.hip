@@ -11,13 +11,14 @@
 // half and quarter runs once per 64 and 32 (128 and 64).
 //
 // What bounds it: the weight stream at 15 to 60 tokens per expert (8 trees x
-// 64 nodes, H = 4096, I = 1536: gate/up streams 3.0 GB in 480 us = 6.3 TB/s,
+// 64 nodes, H = 4096, I = 1536: gate/up streams 3.0 GB in 468 us = 6.4 TB/s,
 // 0.9 of a plain read; replacing the products by an XOR or the row gathers by
 // one row changed nothing), the weight stream and the work per stage together
-// at 120 (32 x 60 nodes, H = 2048, I = 768: 215 us, 128 us with weights from
-// L2).  Against the passes before it (K split over the waves, rows gathered by
-// every wave): gate/up 611 -> 480 and down 363 -> 280 us on the wide layer,
-// 412 -> 215 and 289 -> 127 us at 32 x 60.  No better, same shapes: two tiles
+// at 120 (32 x 60 nodes, H = 2048, I = 768: 200 us; with whole runs everywhere
+// 215, of it 128 with weights from L2).  Against the passes before it (K split over
+// the waves, rows gathered by every wave): gate/up 611 -> 468 and down 363 -> 270 us
+// on the wide layer, 412 -> 200 and 289 -> 122 us at 32 x 60.  fp32: the matrix
+// instructions.  No better, with whole runs at the same shapes: two tiles
 // per wave at three workgroups per CU (482 / 240 us gate/up), four weight
 // stages in flight (484 / 223), K split two ways (486 / 245) or four ways
 // (533 / 376), two M groups for every item (615 / 248).
